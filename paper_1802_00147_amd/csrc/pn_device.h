@@ -137,16 +137,44 @@ __device__ __forceinline__ PnOrbPartials pn_orbit_partials(const PnCoef& k, doub
     return o;
 }
 
-// Right-hand side: f = (dH/dp, -dH/dr, Omega1 x S1, Omega2 x S2).
-__device__ __forceinline__ void pn_rhs_eval(const PnCoef& k, const double* y, double* f) {
+// What an evaluation of the right-hand side needs of the position and the
+// spins alone: u = 1/r, n, the spin-spin weights w_i (dH/dS_i holds u^3 w_i n,
+// eqs. 3-5) and the bracket of dH/dr along n, sum c (5 a a - S.S).  A step's
+// correction leaves exactly these values behind for the state it returns
+// (pn_correct_six), so the next step's first stage takes them over.
+struct PnRhsGeom { double u, nx, ny, nz, w1, w2, Hss5; };
+
+__device__ __forceinline__ PnRhsGeom pn_rhs_geom(const PnCoef& k, const double* y) {
+    const double rx = y[0], ry = y[1], rz = y[2];
+    const double s1x = y[6], s1y = y[7], s1z = y[8];
+    const double s2x = y[9], s2y = y[10], s2z = y[11];
+    PnRhsGeom g;
+    g.u = pn_rsqrt(dot3(rx, ry, rz, rx, ry, rz));
+    g.nx = rx * g.u;
+    g.ny = ry * g.u;
+    g.nz = rz * g.u;
+    const double sn1 = dot3(s1x, s1y, s1z, g.nx, g.ny, g.nz);
+    const double sn2 = dot3(s2x, s2y, s2z, g.nx, g.ny, g.nz);
+    const double S12 = dot3(s1x, s1y, s1z, s2x, s2y, s2z);
+    const double S11 = dot3(s1x, s1y, s1z, s1x, s1y, s1z);
+    const double S22 = dot3(s2x, s2y, s2z, s2x, s2y, s2z);
+    g.w1 = fma(k.m3c12, sn2, k.m6c11 * sn1);
+    g.w2 = fma(k.m3c12, sn1, k.m6c22 * sn2);
+    // w1 a1 + w2 a2 = 6 sum c a a.
+    g.Hss5 = fma(5.0 / 6.0, fma(g.w1, sn1, g.w2 * sn2), -fma(k.c12, S12, fma(k.c11, S11, k.c22 * S22)));
+    return g;
+}
+
+// Right-hand side: f = (dH/dp, -dH/dr, Omega1 x S1, Omega2 x S2), given the
+// geometry of y.
+__device__ __forceinline__ void pn_rhs_eval_g(const PnCoef& k, const PnRhsGeom& g, const double* y, double* f) {
     const double rx = y[0], ry = y[1], rz = y[2];
     const double px = y[3], py = y[4], pz = y[5];
     const double s1x = y[6], s1y = y[7], s1z = y[8];
     const double s2x = y[9], s2y = y[10], s2z = y[11];
-    const double r2 = dot3(rx, ry, rz, rx, ry, rz);
-    const double u = pn_rsqrt(r2);
+    const double u = g.u, nx = g.nx, ny = g.ny, nz = g.nz;
+    const double w1 = g.w1, w2 = g.w2, Hss5 = g.Hss5;
     const double u2 = u * u, u3 = u2 * u, u4 = u2 * u2;
-    const double nx = rx * u, ny = ry * u, nz = rz * u;
     const double P2 = dot3(px, py, pz, px, py, pz);
     const double NP = dot3(nx, ny, nz, px, py, pz);
     const double NP2 = NP * NP;
@@ -161,17 +189,6 @@ __device__ __forceinline__ void pn_rhs_eval(const PnCoef& k, const double* y, do
     const double euy = fma(A1, s1y, A2 * s2y);
     const double euz = fma(A1, s1z, A2 * s2z);
     const double LSu = dot3(Lx, Ly, Lz, eux, euy, euz);   // u^3 L.S_eff
-    const double sn1 = dot3(s1x, s1y, s1z, nx, ny, nz);
-    const double sn2 = dot3(s2x, s2y, s2z, nx, ny, nz);
-    const double S12 = dot3(s1x, s1y, s1z, s2x, s2y, s2z);
-    const double S11 = dot3(s1x, s1y, s1z, s1x, s1y, s1z);
-    const double S22 = dot3(s2x, s2y, s2z, s2x, s2y, s2z);
-    // Spin-spin weights: dH/dS_i holds u^3 w_i n (eqs. 3-5).
-    const double w1 = fma(k.m3c12, sn2, k.m6c11 * sn1);
-    const double w2 = fma(k.m3c12, sn1, k.m6c22 * sn2);
-    // Bracket of dH/dr along n (eqs. 3-5): sum c (5 a a - S.S), with
-    // w1 a1 + w2 a2 = 6 sum c a a.
-    const double Hss5 = fma(5.0 / 6.0, fma(w1, sn1, w2 * sn2), -fma(k.c12, S12, fma(k.c11, S11, k.c22 * S22)));
 
     // dH/dp = cp p + HNP n + u^3 (S_eff x r).
     f[0] = fma(euy, rz, fma(-euz, ry, fma(HNP, nx, o.cp * px)));
@@ -200,6 +217,10 @@ __device__ __forceinline__ void pn_rhs_eval(const PnCoef& k, const double* y, do
     f[9] = o2y * s2z - o2z * s2y;
     f[10] = o2z * s2x - o2x * s2z;
     f[11] = o2x * s2y - o2y * s2x;
+}
+
+__device__ __forceinline__ void pn_rhs_eval(const PnCoef& k, const double* y, double* f) {
+    pn_rhs_eval_g(k, pn_rhs_geom(k, y), y, f);
 }
 
 // Quantities of the spins alone, fixed while a correction moves r and p:
@@ -347,19 +368,30 @@ __device__ __forceinline__ double pn_rcp1(double x) {
 // Energy restoration by momentum scaling: Newton on a for
 // g(a) = H(r, a p, S) - E0 using the polynomial form of H in a.
 // Returns the iteration count; *conv is false if max_iter was reached.
+// The first iteration, at a = 1, stands by itself: its powers of a are 1, and
+// after the projection it is nearly always the last.  Its sums are the
+// general iteration's with exact factors left out (contraction is off: a
+// coefficient's own product is rounded first there, too).
 __device__ __forceinline__ int pn_energy_scale_poly(const PnEnergyPoly& e, double* y, double E0, double tol,
                                                     int max_iter, bool& conv) {
-    double a = 1.0;
-    int it = 0;
-    conv = false;
-    while (it < max_iter) {
+    double a;
+    {
+#pragma clang fp contract(off)
+        const double g = (((e.K6 + e.K4) + e.K2) + (e.K1 + e.K0)) - E0;
+        const double dg = fma(4.0, e.K4, 6.0 * e.K6) + fma(2.0, e.K2, e.K1);
+        const double da = -g * pn_rcp1(dg);
+        a = 1.0 + da;
+        conv = fabs(da) <= tol;
+    }
+    int it = 1;                          // max_iter >= 1
+    while (!conv && it < max_iter) {
         const double a2 = a * a, a3 = a2 * a;
         const double g = fma(fma(fma(e.K6, a2, e.K4), a2, e.K2), a2, fma(e.K1, a, e.K0)) - E0;
         const double dg = fma(fma(6.0 * e.K6, a2, 4.0 * e.K4), a3, fma(2.0 * e.K2, a, e.K1));
         const double da = -g * pn_rcp1(dg);
         a += da;
         ++it;
-        if (fabs(da) <= tol) { conv = true; break; }
+        conv = fabs(da) <= tol;
     }
     y[3] *= a; y[4] *= a; y[5] *= a;
     return it;
@@ -421,9 +453,10 @@ __device__ __forceinline__ void pn_project_EJ_g(const PnCoef& k, const PnSpinInv
 // The six-integral correction after the spin lengths: `sweeps` passes of the
 // joint projection followed by the energy's momentum scaling.  The spins do
 // not move, and the momentum scaling leaves r (so its geometry) unchanged:
-// the geometry computed for the scaling serves the next pass's projection.
+// the geometry computed for the scaling serves the next pass's projection
+// and, in *next, the right-hand side of the state returned (sweeps >= 1).
 __device__ __forceinline__ int pn_correct_six(const PnCoef& k, double* y, const double* ref, double tol,
-                                              int max_iter, int sweeps, bool& noconv) {
+                                              int max_iter, int sweeps, bool& noconv, PnRhsGeom& next) {
     const PnSpinInv si = pn_spin_inv(k, y);
     PnRGeom geo = pn_rgeom(k, si, y);
     int iters = 0;
@@ -434,6 +467,7 @@ __device__ __forceinline__ int pn_correct_six(const PnCoef& k, double* y, const 
         iters += pn_energy_scale_poly(pn_energy_poly_g(k, si, geo, y), y, ref[0], tol, max_iter, conv);
         noconv = noconv || !conv;
     }
+    next = PnRhsGeom{geo.u, geo.nx, geo.ny, geo.nz, geo.w1, geo.w2, geo.Hss5};
     return iters;
 }
 
@@ -487,26 +521,31 @@ __device__ __forceinline__ int pn_dual_scale(const PnCoef& k, double* y, const d
 }
 
 // One correction against ref = (E0, J0x, J0y, J0z); returns Newton iterations.
+// kPnCarriesGeom<MODE>: it leaves the corrected state's geometry in next.
+template <int MODE>
+constexpr bool kPnCarriesGeom = MODE == PN_CORR_SIX;
+
 template <int MODE>
 __device__ __forceinline__ int pn_correct(const PnCoef& k, double* y, const double* ref, double tol,
-                                          int max_iter, int sweeps, bool& noconv) {
+                                          int max_iter, int sweeps, bool& noconv, PnRhsGeom& next) {
     noconv = false;
     if (MODE == PN_CORR_NONE) return 0;
     pn_correct_spins(k, y);
     if (MODE == PN_CORR_SPIN) return 0;
-    if (MODE == PN_CORR_SIX) return pn_correct_six(k, y, ref, tol, max_iter, sweeps, noconv);
+    if (MODE == PN_CORR_SIX) return pn_correct_six(k, y, ref, tol, max_iter, sweeps, noconv, next);
     bool conv = true;
     const int iters = pn_dual_scale(k, y, ref, tol, max_iter, conv);
     noconv = !conv;
     return iters;
 }
 
-// One fixed step of RK4 or of the Dormand-Prince fifth-order weights.
+// One fixed step of RK4 or of the Dormand-Prince fifth-order weights, from y
+// whose geometry is g.
 template <int METHOD>
-__device__ __forceinline__ void pn_rk_step(const PnCoef& k, double* y, double h) {
+__device__ __forceinline__ void pn_rk_step(const PnCoef& k, const PnRhsGeom& g, double* y, double h) {
     double kk[12], acc[12], t[12];
     if (METHOD == PN_RK4) {
-        pn_rhs_eval(k, y, kk);
+        pn_rhs_eval_g(k, g, y, kk);
 #pragma unroll
         for (int c = 0; c < 12; ++c) { acc[c] = kk[c]; t[c] = fma(0.5 * h, kk[c], y[c]); }
         pn_rhs_eval(k, t, kk);
@@ -533,7 +572,7 @@ __device__ __forceinline__ void pn_rk_step(const PnCoef& k, double* y, double h)
     constexpr double b1 = 35.0 / 384.0, b3 = 500.0 / 1113.0, b4 = 125.0 / 192.0,
                      b5 = -2187.0 / 6784.0, b6 = 11.0 / 84.0;
     double s3[12], s4[12], s5[12], s6[12];
-    pn_rhs_eval(k, y, kk);  // k1
+    pn_rhs_eval_g(k, g, y, kk);  // k1
 #pragma unroll
     for (int c = 0; c < 12; ++c) {
         t[c] = fma(h * a21, kk[c], y[c]);

@@ -147,7 +147,8 @@ __global__ __launch_bounds__(kBlock) void k_correct(ParamArgs pa, CorrArgs ca, i
 #pragma unroll
     for (int c = 0; c < 4; ++c) r[c] = ref[c * ld + i];
     bool nc = false;
-    const int it = pn_correct<MODE>(k, s, r, ca.tol, ca.max_iter, ca.sweeps, nc);
+    PnRhsGeom unused;
+    const int it = pn_correct<MODE>(k, s, r, ca.tol, ca.max_iter, ca.sweeps, nc, unused);
     store_state(y, ld, i, s);
     if (iters) iters[i] = nc ? -it : it;
 }
@@ -180,13 +181,16 @@ __global__ __launch_bounds__(kBlock) void k_step(ParamArgs pa, CorrArgs ca, doub
     const double eta = RR ? orbit_eta(pa, i, eta0) : 0.0;
     int64_t left = every;
     double* row = traj;
+    PnRhsGeom geo;
+    if constexpr (!RR && kPnCarriesGeom<MODE>) geo = pn_rhs_geom(k, s);
     for (int64_t t = 0; t < nsteps; ++t) {
+        if constexpr (!RR && !kPnCarriesGeom<MODE>) geo = pn_rhs_geom(k, s);
         if constexpr (RR)
             pn_rk_step_rr<METHOD>(k, eta, z, h);
         else
-            pn_rk_step<METHOD>(k, s, h);
+            pn_rk_step<METHOD>(k, geo, s, h);
         bool nc;
-        pn_correct<MODE>(k, s, r, ca.tol, ca.max_iter, ca.sweeps, nc);
+        pn_correct<MODE>(k, s, r, ca.tol, ca.max_iter, ca.sweeps, nc, geo);
         if (row != nullptr && --left == 0) {
             store_state(row, ld, i, s);
             row += 12 * ld;
@@ -279,6 +283,7 @@ __device__ __forceinline__ double swap_pair(double v) {
 // lane its shadow, so every lane holds a single trajectory.
 struct PairState {
     double y[12], ref[4];
+    PnRhsGeom geo;                  // of y: what the next step's first stage starts from
     double acc, d2, t_end;
     int64_t t, nsteps, renorms;
     int st, nmax;
@@ -326,26 +331,41 @@ __device__ __forceinline__ void pair_begin(PairState& ps, const PnCoef& k, bool 
     ps.renorms = 0;
     ps.nmax = 0;
     ps.any_nc = false;
+    ps.geo = pn_rhs_geom(k, ps.y);
 }
 
 // One step of both trajectories (each lane its own), then the pair's
 // validity, separation and, rarely, the shadow's renormalisation.
+// The kernel is bound by the instructions it issues (FP64, four cycles each),
+// so what a step can take over it does not form again: the first stage's
+// geometry comes from the correction, and a finite separation shows that every
+// component of both states is finite (e = y - y' is NaN or infinite if either
+// is), so the component test runs only where the separation is not finite or
+// a radius leaves its bounds.  RK4 with six integrals: 1,383 FP64 instructions
+// a step in the loop (1,443 with both formed again and a general first Newton
+// iteration); 4,096 orbits, 5,000 steps: 14.19 ms (15.26), 98,596 orbits, 4,000
+// steps: 41.7 ms (44.1).
 template <int METHOD, int MODE>
 __device__ __forceinline__ void pair_step(PairState& ps, const PnCoef& k, bool shadow, const FliArgs& fa,
                                           int64_t i) {
     bool nc;
-    pn_rk_step<METHOD>(k, ps.y, fa.h);
-    const int it = pn_correct<MODE>(k, ps.y, ps.ref, fa.corr.tol, fa.corr.max_iter, fa.corr.sweeps, nc);
+    if constexpr (!kPnCarriesGeom<MODE>) ps.geo = pn_rhs_geom(k, ps.y);
+    pn_rk_step<METHOD>(k, ps.geo, ps.y, fa.h);
+    const int it = pn_correct<MODE>(k, ps.y, ps.ref, fa.corr.tol, fa.corr.max_iter, fa.corr.sweeps, nc, ps.geo);
     ps.any_nc = ps.any_nc || nc;
     ps.nmax = max(ps.nmax, it);
     ps.t += 1;
-    // Orbit verdict first, then the shadow's (same order in both lanes).
-    const int mine = pn_validity(ps.y, fa.rmerge2, fa.resc2);
-    const int other = swap_pair_i32(mine);
-    const int vo = shadow ? other : mine, vs = shadow ? mine : other;
-    ps.st = vo != PN_ORBIT_OK ? vo : vs;
-    if (ps.st != PN_ORBIT_OK) return;
+    const double r2 = dot3(ps.y[0], ps.y[1], ps.y[2], ps.y[0], ps.y[1], ps.y[2]);
     ps.d2 = pair_d2(ps.y);
+    const bool fine = r2 >= fa.rmerge2 && r2 <= fa.resc2 && isfinite(ps.d2);
+    if (__ballot(!fine) != 0ull) {
+        // Orbit verdict first, then the shadow's (same order in both lanes).
+        const int mine = pn_validity(ps.y, fa.rmerge2, fa.resc2);
+        const int other = swap_pair_i32(mine);
+        const int vo = shadow ? other : mine, vs = shadow ? mine : other;
+        ps.st = vo != PN_ORBIT_OK ? vo : vs;
+        if (ps.st != PN_ORBIT_OK) return;
+    }
     if (ps.d2 >= fa.d_renorm2) {
         const double d = sqrt(ps.d2);
         ps.acc += log10(d / fa.d0);
@@ -358,6 +378,7 @@ __device__ __forceinline__ void pair_step(PairState& ps, const PnCoef& k, bool s
             for (int c = 0; c < 12; ++c) ps.y[c] = fma(f, ps.y[c] - yp[c], yp[c]);
             pn_correct_spins(k, ps.y);
             capture_ref(k, ps.y, ps.ref);
+            ps.geo = pn_rhs_geom(k, ps.y);
         }
         ps.renorms += 1;
         ps.d2 = pair_d2(ps.y);
@@ -598,6 +619,7 @@ __global__ __launch_bounds__(256, OCC) void k_batch_scan(ParamArgs pa, FliArgs f
                         if (i >= 0 && i < fa.n) {
                             cur = i;
                             load_coef(pa, cur, k);
+                            ps.geo = pn_rhs_geom(k, ps.y);
                         }
                     }
                 }
@@ -767,7 +789,9 @@ __device__ __forceinline__ void wrap_open(PairState& ps, PnCoef& k, const ParamA
     if (!match) {
         pair_ends(ps, fa, p.orbit);
         ps.st = PN_ORBIT_BADPARAM;
+        return;
     }
+    ps.geo = pn_rhs_geom(k, ps.y);
 }
 
 // SHARED: every orbit has the parameter set of pa.coef, whose table then stays
