@@ -394,6 +394,24 @@ __device__ __forceinline__ bool pair_running(const PairState& ps) {
     return ps.st == PN_ORBIT_OK && ps.t < ps.nsteps;
 }
 
+// Steps the wavefront runs before its next look for ended orbits or pieces:
+// up to the first one that ends (left: steps this pair still has to run; a
+// pair without work gives a large value), at least kMinRun, at most cap.  A
+// fixed run of c steps left every ended pair idle for c / 2 steps on average;
+// stopping at the first end costs one look, about half a step, per end, and
+// kMinRun takes the ends that lie close together in one.  98,596 orbits of
+// 4,000 steps, balanced, chunks of 256: 41.7 ms with fixed runs, 37.2 with these
+// (1,716 -> 1,480 vector instructions per wavefront and step of work).
+constexpr int kMinRun = 16;
+
+__device__ __forceinline__ int wave_run(int64_t left, int32_t cap) {
+    int m = left < (int64_t)cap ? (int)left : cap;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = min(m, __shfl_xor(m, off));
+    m = max(m, kMinRun);
+    return __builtin_amdgcn_readfirstlane(min(m, cap));
+}
+
 // Final separation and outputs of orbit i (written by the orbit lane).
 __device__ __forceinline__ void pair_finish(PairState& ps, const PnCoef& k, bool shadow, const FliArgs& fa,
                                             int64_t i) {
@@ -651,8 +669,11 @@ __global__ __launch_bounds__(256, OCC) void k_batch_scan(ParamArgs pa, FliArgs f
             }
         }
         if (__ballot(cur >= 0) == 0ull) break;
+        // A checkpointed launch counts whole chunks; the others stop at the
+        // first orbit that ends.
+        const int run = CKPT ? chunk : wave_run(cur < 0 ? (int64_t)chunk : pair_running(ps) ? ps.nsteps - ps.t : 0, chunk);
         if (cur >= 0) {
-            for (int c = 0; c < chunk && pair_running(ps); ++c) pair_step<METHOD, MODE>(ps, k, shadow, fa, cur);
+            for (int c = 0; c < run && pair_running(ps); ++c) pair_step<METHOD, MODE>(ps, k, shadow, fa, cur);
             if (!pair_running(ps)) {
                 pair_finish(ps, k, shadow, fa, cur);
                 cur = -1;
@@ -830,10 +851,11 @@ __global__ __launch_bounds__(256, OCC) void k_wrap_scan(ParamArgs pa, FliArgs fa
                                   shadow);
             open = false;
         }
+        // Steps left in this launch: up to b, less what lies past tend.
+        const int64_t stop = pend <= tend ? b : b - (pend - tend);
+        const int run = wave_run(!active ? (int64_t)wa.chunk : ps.st == PN_ORBIT_OK ? stop - ps.t : 0, wa.chunk);
         if (active) {
-            // Steps left in this launch: up to b, less what lies past tend.
-            const int64_t stop = pend <= tend ? b : b - (pend - tend);
-            for (int c = 0; c < wa.chunk && ps.st == PN_ORBIT_OK && ps.t < stop; ++c)
+            for (int c = 0; c < run && ps.st == PN_ORBIT_OK && ps.t < stop; ++c)
                 pair_step<METHOD, MODE>(ps, k, shadow, fa, orbit);
             if (!(ps.st == PN_ORBIT_OK && ps.t < stop)) {
                 if (pend > tend) {
