@@ -345,13 +345,23 @@ __device__ __forceinline__ void pair_begin(PairState& ps, const PnCoef& k, bool 
 // a step in the loop (1,443 with both formed again and a general first Newton
 // iteration); 4,096 orbits, 5,000 steps: 14.19 ms (15.26), 98,596 orbits, 4,000
 // steps: 41.7 ms (44.1).
+// Wavefront priority: of two wavefronts on a SIMD the older one issues
+// whenever it can, so the younger one would wait until it has ended and then
+// run alone, with nobody to fill the cycles in which its own results are
+// pending.  Each wavefront therefore drops to low priority for the last 7% of
+// a step: there the other one takes over, for about a step.  Both stay in
+// flight to the end (an issue in 94-96% of the cycles instead of 87-89%):
+// 400,000 uneven orbits 85.2 -> 77.4 ms, 98,596 orbits, 4,000 steps, 37.4 -> 36.3;
+// low for half the step or for a dozen instructions gains nothing.
 template <int METHOD, int MODE>
 __device__ __forceinline__ void pair_step(PairState& ps, const PnCoef& k, bool shadow, const FliArgs& fa,
                                           int64_t i) {
     bool nc;
+    __builtin_amdgcn_s_setprio(1);
     if constexpr (!kPnCarriesGeom<MODE>) ps.geo = pn_rhs_geom(k, ps.y);
     pn_rk_step<METHOD>(k, ps.geo, ps.y, fa.h);
     const int it = pn_correct<MODE>(k, ps.y, ps.ref, fa.corr.tol, fa.corr.max_iter, fa.corr.sweeps, nc, ps.geo);
+    __builtin_amdgcn_s_setprio(0);
     ps.any_nc = ps.any_nc || nc;
     ps.nmax = max(ps.nmax, it);
     ps.t += 1;
