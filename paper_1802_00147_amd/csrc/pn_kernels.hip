@@ -508,10 +508,27 @@ __global__ __launch_bounds__(256) void k_batch_clear(BatchWs ws) {
     for (int b = t; b < 2 * kBins; b += 256) ws.bins[b] = 0u;
 }
 
+// Counting and scattering take kBinItems orbits per lane and count in LDS
+// first: the step counts of a batch fall into a few dozen bins, and one global
+// atomic per orbit on so few addresses ran at 0.8 per nanosecond (400,000
+// orbits: 505 us for the count, 508 for the scatter).  One per workgroup and
+// occupied bin leaves 8.6 and 9.4 us.
+constexpr int kBinItems = 4;
+static_assert(kBins == 256, "one lane per bin");
+
 __global__ __launch_bounds__(256) void k_batch_bin_count(BatchWs ws, const double* t_end, double h, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    atomicAdd(&ws.bins[step_bin(t_end[i], h)], 1u);
+    __shared__ unsigned int cnt[kBins];
+    const int t = threadIdx.x;
+    cnt[t] = 0u;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * (256 * kBinItems) + t;
+#pragma unroll
+    for (int q = 0; q < kBinItems; ++q) {
+        const int64_t i = base + 256 * q;
+        if (i < n) atomicAdd(&cnt[step_bin(t_end[i], h)], 1u);
+    }
+    __syncthreads();
+    if (cnt[t] != 0u) atomicAdd(&ws.bins[t], cnt[t]);
 }
 
 // Exclusive prefix sum of the bin counters into the offsets (one workgroup).
@@ -530,10 +547,29 @@ __global__ __launch_bounds__(kBins) void k_batch_bin_scan(BatchWs ws) {
 }
 
 __global__ __launch_bounds__(256) void k_batch_bin_scatter(BatchWs ws, const double* t_end, double h, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const unsigned int pos = atomicAdd(&ws.bins[kBins + step_bin(t_end[i], h)], 1u);
-    ws.order[pos] = (int32_t)i;
+    __shared__ unsigned int cnt[kBins];              // orbits of this workgroup, then their first position
+    const int t = threadIdx.x;
+    cnt[t] = 0u;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * (256 * kBinItems) + t;
+    int bin[kBinItems];
+    unsigned int rank[kBinItems];
+#pragma unroll
+    for (int q = 0; q < kBinItems; ++q) {
+        const int64_t i = base + 256 * q;
+        bin[q] = -1;
+        if (i < n) {
+            bin[q] = step_bin(t_end[i], h);
+            rank[q] = atomicAdd(&cnt[bin[q]], 1u);
+        }
+    }
+    __syncthreads();
+    const unsigned int mine = cnt[t];
+    if (mine != 0u) cnt[t] = atomicAdd(&ws.bins[kBins + t], mine);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kBinItems; ++q)
+        if (bin[q] >= 0) ws.order[cnt[bin[q]] + rank[q]] = (int32_t)(base + 256 * q);
 }
 
 // A table of saved orbit pairs: record r holds the orbit index and the exact
@@ -1223,12 +1259,12 @@ pn_status prepare_scan(const pn_model* model, const pn_params& params, const pn_
 void enqueue_batch(int method, int mode, const ParamArgs& pa, const FliArgs& fa, const BatchWs& w,
                    const pn_tuning& tu, int ncu, hipStream_t stream, const CkptArgs* ck = nullptr,
                    bool resume = false) {
-    const unsigned g256 = (unsigned)((fa.n + 255) / 256);
+    const unsigned gbin = (unsigned)((fa.n + 256 * kBinItems - 1) / (256 * kBinItems));
     if (!resume) {
         hipLaunchKernelGGL(k_batch_clear, dim3(1), dim3(256), 0, stream, w);
-        hipLaunchKernelGGL(k_batch_bin_count, dim3(g256), dim3(256), 0, stream, w, fa.t_end, fa.h, fa.n);
+        hipLaunchKernelGGL(k_batch_bin_count, dim3(gbin), dim3(256), 0, stream, w, fa.t_end, fa.h, fa.n);
         hipLaunchKernelGGL(k_batch_bin_scan, dim3(1), dim3(kBins), 0, stream, w);
-        hipLaunchKernelGGL(k_batch_bin_scatter, dim3(g256), dim3(256), 0, stream, w, fa.t_end, fa.h, fa.n);
+        hipLaunchKernelGGL(k_batch_bin_scatter, dim3(gbin), dim3(256), 0, stream, w, fa.t_end, fa.h, fa.n);
         if (ck) hipLaunchKernelGGL(k_ckpt_clear, dim3(1), dim3(64), 0, stream, *ck);
     }
     if (method == PN_RK4)
