@@ -8,10 +8,10 @@
 // its eight K values with one 16-byte LDS load, and fused epilogues (bias as
 // the accumulators' start, ReLU, ReLU-mask of the backward pass, FP32 and/or
 // bfloat16 stores).  Arbitrary strides let the same kernel form X W^T, G W
-// and G^T H; k_gemm_group runs a training step's four weight gradients in one
-// launch.  A training step's forward pass, loss and layer gradients run in
-// one kernel, k_mlp_train, and inference over scan grids in one persistent
-// kernel, k_mlp_infer, both with the same arithmetic as k_gemm_bf16.  The
+// and G^T H.  A training step is two kernels: k_mlp_train (forward pass, loss,
+// layer gradients) and k_mlp_update (weight and bias gradients, Adam).
+// Inference over scan grids is one persistent kernel, k_mlp_infer.  All take
+// their products with the same arithmetic as k_gemm_bf16.  The
 // surrogate-assisted scan (pn_surrogate_scan) strings these together with
 // the FP64 scans.
 #include <hip/hip_runtime.h>
@@ -77,8 +77,6 @@ struct GemmArgs {
     int64_t ldcb;
     int relu;
     int amode, bmode;          // operand staging: 0 element-wise, 1 K contiguous, 2 M (N) contiguous
-    int kchunk;                // K range of one workgroup layer (blockIdx.z); K when not split
-    int64_t split_stride;      // Cf offset between K splits (0 when not split)
 };
 
 // Staging modes of an operand whose element (r, k) -- r the row of the
@@ -171,35 +169,32 @@ __device__ __forceinline__ void stage_tiles(uint16_t (*tiles)[BM][LDSK], int ns,
     for (int s = 0; s < ns; ++s) store_chunk(tiles[s], load_chunk(p, sr, sk, mode, r0, R, k0 + s * BK, K, tid), mode, tid);
 }
 
-// One 64 x 64 output tile (column block bx, row block by, K split bz) of
-// C = A B (+ bias) (ReLU) (* mask), FP32 accumulation, staged through As/Bt
+// C = A B (+ bias) (ReLU) (* mask), M x N: grid (N / 64, M / 64), one 64 x 64
+// output tile per workgroup, FP32 accumulation, staged through LDS
 // (kStageSlices K slices each).  The MFMAs take the K slices in increasing
 // order, one 16x16x32 step per slice and output block.
-__device__ __forceinline__ void gemm_block(const GemmArgs& g, int bx, int by, int bz, uint16_t (*As)[BM][LDSK],
-                                           uint16_t (*Bt)[BN][LDSK]) {
+__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
+    __shared__ __attribute__((aligned(16))) uint16_t As[kStageSlices][BM][LDSK];
+    __shared__ __attribute__((aligned(16))) uint16_t Bt[kStageSlices][BN][LDSK];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int64_t m0 = (int64_t)by * BM, n0 = (int64_t)bx * BN;
+    const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = (int64_t)blockIdx.x * BN;
     const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
     const int lr = lane & 15, lk = (lane >> 4) * 8;
-    // The bias (never with split K) is the accumulators' starting value: the
-    // MFMAs add the K slices to it.
+    // The bias is the accumulators' starting value: the MFMAs add the K slices
+    // to it.
     f32x4 acc[2][2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int64_t n = n0 + wn + 16 * j + lr;
-        const float b0 = (g.bias && bz == 0 && n < g.N) ? g.bias[n] : 0.0f;
+        const float b0 = (g.bias && n < g.N) ? g.bias[n] : 0.0f;
 #pragma unroll
         for (int i = 0; i < 2; ++i) acc[i][j] = f32x4{b0, b0, b0, b0};
     }
-    // Split K: layer z of the grid sums K range [kb, ke) into its own partial.
-    const int64_t kb = (int64_t)bz * g.kchunk;
-    const int64_t ke = (kb + g.kchunk < g.K) ? kb + g.kchunk : g.K;
-    float* const Cf = g.Cf ? g.Cf + (int64_t)bz * g.split_stride : nullptr;
-    for (int64_t k0 = kb; k0 < ke; k0 += kStageSlices * BK) {
-        const int64_t left = (ke - k0 + BK - 1) / BK;
+    for (int64_t k0 = 0; k0 < g.K; k0 += kStageSlices * BK) {
+        const int64_t left = (g.K - k0 + BK - 1) / BK;
         const int ns = left < kStageSlices ? (int)left : kStageSlices;
-        stage_tiles(As, ns, g.A, g.sam, g.sak, g.amode, m0, g.M, k0, ke, tid);
-        stage_tiles(Bt, ns, g.B, g.sbn, g.sbk, g.bmode, n0, g.N, k0, ke, tid);
+        stage_tiles(As, ns, g.A, g.sam, g.sak, g.amode, m0, g.M, k0, g.K, tid);
+        stage_tiles(Bt, ns, g.B, g.sbn, g.sbk, g.bmode, n0, g.N, k0, g.K, tid);
         __syncthreads();
 #pragma unroll
         for (int s = 0; s < kStageSlices; ++s) {
@@ -230,99 +225,12 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& g, int bx, int by, in
                 if (m >= g.M || n >= g.N) continue;
                 const float x = acc[i][j][v];
                 const bool keep = !g.mask || bf2f(g.mask[m * g.ldm + n]) > 0.0f;
-                if (Cf) Cf[m * g.ldcf + n] = keep ? (g.relu ? fmaxf(x, 0.0f) : x) : 0.0f;
+                if (g.Cf) g.Cf[m * g.ldcf + n] = keep ? (g.relu ? fmaxf(x, 0.0f) : x) : 0.0f;
                 if (g.Cb) {
                     const uint16_t y = g.relu ? relu_bf16(f2bf(x)) : f2bf(x);
                     g.Cb[m * g.ldcb + n] = keep ? y : (uint16_t)0;
                 }
             }
-}
-
-// C = A B (+ bias) (ReLU) (* mask), M x N: grid (N / 64, M / 64, K splits).
-__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
-    __shared__ __attribute__((aligned(16))) uint16_t As[kStageSlices][BM][LDSK];
-    __shared__ __attribute__((aligned(16))) uint16_t Bt[kStageSlices][BN][LDSK];
-    gemm_block(g, blockIdx.x, blockIdx.y, blockIdx.z, As, Bt);
-}
-
-// Up to four independent products in one launch (the weight gradients of a
-// training step): block b belongs to product l with first[l] <= b <
-// first[l+1] and takes its tile in x-fastest order of that product's
-// (tx, ty, splits) grid.  Each tile is computed as k_gemm_bf16 computes it.
-// Bias gradients: db_l[n] = sum over rows of the bfloat16 gradient G_l
-// [rows x N_l]; blocks first[l] <= b < first[l+1] serve layer l, column
-// n = b - first[l], one column per 256-thread block.
-struct BiasArgs {
-    const uint16_t* G[4];
-    int64_t ldg[4];
-    float* db[4];
-    int first[5];
-    int64_t rows;
-};
-
-__device__ __forceinline__ void bias_block(const BiasArgs& a, int b, float* part) {
-    int l = 0;
-#pragma unroll
-    for (int k = 1; k < 4; ++k) l += (b >= a.first[k]) ? 1 : 0;
-    const int n = b - a.first[l];
-    const uint16_t* G = a.G[l];
-    const int64_t ldg = a.ldg[l], rows = a.rows;
-    float* db = a.db[l];
-    float s = 0.0f;
-    for (int64_t m = threadIdx.x; m < rows; m += 256) s += bf2f(G[m * ldg + n]);
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) part[threadIdx.x] += part[threadIdx.x + k];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) db[n] = part[0];
-}
-
-// The weight-gradient products and, after their blocks (first[4] onwards),
-// the bias-gradient columns of BiasArgs: the whole backward reduction of a
-// training step in one launch.
-struct GemmGroup {
-    GemmArgs g[4];
-    int tx[4], ty[4];
-    int first[5];
-    BiasArgs bias;
-};
-__global__ __launch_bounds__(256) void k_gemm_group(GemmGroup gg) {
-    __shared__ __attribute__((aligned(16))) uint16_t As[kStageSlices][BM][LDSK];
-    __shared__ __attribute__((aligned(16))) uint16_t Bt[kStageSlices][BN][LDSK];
-    __shared__ float part[256];
-    const int b = blockIdx.x;
-    if (b >= gg.first[4]) {
-        bias_block(gg.bias, b - gg.first[4], part);
-        return;
-    }
-    int l = 0;
-#pragma unroll
-    for (int k = 1; k < 4; ++k) l += (b >= gg.first[k]) ? 1 : 0;
-    int tx = gg.tx[0], ty = gg.ty[0], f = gg.first[0];
-    if (l == 1) { tx = gg.tx[1]; ty = gg.ty[1]; f = gg.first[1]; }
-    if (l == 2) { tx = gg.tx[2]; ty = gg.ty[2]; f = gg.first[2]; }
-    if (l == 3) { tx = gg.tx[3]; ty = gg.ty[3]; f = gg.first[3]; }
-    const int local = b - f;
-    const int bx = local % tx, by = (local / tx) % ty, bz = local / (tx * ty);
-    switch (l) {
-        case 0: gemm_block(gg.g[0], bx, by, bz, As, Bt); break;
-        case 1: gemm_block(gg.g[1], bx, by, bz, As, Bt); break;
-        case 2: gemm_block(gg.g[2], bx, by, bz, As, Bt); break;
-        default: gemm_block(gg.g[3], bx, by, bz, As, Bt); break;
-    }
-}
-
-// C[m][n] (ld ldc) = sum over z = 0 .. splits-1, in that order, of part[z][m][n].
-__global__ __launch_bounds__(256) void k_sum_splits(const float* part, int splits, int M, int N, float* C,
-                                                    int64_t ldc) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t mn = (int64_t)M * N;
-    if (e >= mn) return;
-    float x = 0.0f;
-    for (int z = 0; z < splits; ++z) x += part[z * mn + e];
-    C[(e / N) * ldc + e % N] = x;
 }
 
 // Rows idx[b] (or b) of the FP32 features -> bfloat16 [rows x 8].
@@ -342,315 +250,294 @@ __device__ __forceinline__ bf16x8 load_bf16x8(const uint16_t* p) {
     return *reinterpret_cast<const bf16x8*>(p);
 }
 
+// Fragment order of a 256 x 256 bfloat16 operand whose element (col, k) is the
+// product's column col at depth k: the 16-byte piece of lane l for column
+// block cb (16 columns) and K slice sl (32 deep) -- column 16 cb + l % 16, depths
+// 32 sl + 8 (l / 16) .. + 8 -- is piece (cb * 8 + sl) * 64 + l, so a wavefront loads
+// a fragment as 1 KB in a row.
+// (cb is the same in all lanes of a wavefront: the address is a scalar base and
+// one 32-bit lane offset.)
+__device__ __forceinline__ bf16x8 load_frag(const uint16_t* F, int cb, int sl, int lane) {
+    const char* base = reinterpret_cast<const char*>(F) + __builtin_amdgcn_readfirstlane(cb * 8 + sl) * 1024;
+    return *reinterpret_cast<const bf16x8*>(base + (uint32_t)(lane * 16));
+}
+
 // What the training pass reads and leaves behind: rows idx[r] of the
 // features; the gathered bfloat16 inputs x_out [n][8] and hidden activations
-// h_out[l] [n][256] (16-byte aligned) for the weight gradients; the batch's
-// mean loss added to *loss and its gradient with respect to the two outputs
-// in gout [n][2]; the layer gradients g3 = (g4 W4) * (h3 > 0),
-// g2 = (g3 W3) * (h2 > 0) and g1 = (g2 W2) * (h1 > 0) in g3_out, g2_out,
-// g1_out [n][256] (all bfloat16).  The backward products take their B
-// operands from wT[1] = W3^T and wT[0] = W2^T ([in][out] bfloat16 copies, so
-// that a fragment's K values are contiguous).
+// h_out[l] [n][256] (16-byte aligned); the batch's mean loss added to *loss
+// and its gradient with respect to the two outputs in gout [n][2]; the layer
+// gradients g3 = (g4 W4) * (h3 > 0), g2 = (g3 W3) * (h2 > 0) and g1 = (g2 W2) * (h1 > 0)
+// in g_out[2], [1], [0] [n][256] (all bfloat16).  The same tensors go out a
+// second time in row-block order, element (r, c) of C columns at
+// ((r / 8) C + c) 8 + r % 8, with zeros in the rows from n up to the next multiple
+// of 32: there the eight rows that a lane of the weight gradients' products
+// takes lie together.  Hidden weights come in fragment order: wf[0], wf[1] =
+// W2, W3 (columns: outputs), wt[0], wt[1] = W2, W3 transposed (columns: inputs);
+// W1 comes with its rows padded to eight values.
 struct TrainIO {
-    const int32_t* idx;
-    uint16_t* x_out;
-    uint16_t* h_out[3];
+    const uint16_t* w0;              // layer 1 [256][8]
+    const uint16_t* w3;              // layer 4 [2][256]
+    const float* b[4];
+    const uint16_t* wf[2];
+    const uint16_t* wt[2];
+    const float* feat;
     const float* label;
     const float* target;
-    uint16_t* gout;
+    const int32_t* idx;
+    int64_t n;
+    float* out;
     float* loss;
-    uint16_t* g3_out;
-    uint16_t* g2_out;
-    uint16_t* g1_out;
-    const uint16_t* wT[2];
+    uint16_t* x_out;
+    uint16_t* h_out[3];
+    uint16_t* gout;
+    uint16_t* g_out[3];
+    uint16_t* xT;                    // row-block order
+    uint16_t* hT[3];
+    uint16_t* g4T;
+    uint16_t* gT[3];
 };
 
-// Exchange with the adjacent lane (lanes 2j and 2j + 1), DPP quad permutation
-// [1, 0, 3, 2].
-__device__ __forceinline__ float swap_adjacent(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
-}
+constexpr int kTrainFT = 16;        // rows of a training tile
 
-// Copy the valid rows of an LDS activation tile to global memory, 16 bytes
-// per access.
-template <int FT>
-__device__ __forceinline__ void copy_tile(const uint16_t (*h)[FLD], uint16_t* dst, int64_t r0, int64_t n, int tid) {
-#pragma unroll
-    for (int e = tid; e < FT * 32; e += 512) {
-        const int r = e >> 5, c = (e & 31) * 8;
-        if (r0 + r < n) *reinterpret_cast<uint4*>(dst + (r0 + r) * 256 + c) = *reinterpret_cast<const uint4*>(&h[r][c]);
-    }
-}
-
-// Training pass of one step over the batch rows, in tiles of FT rows (a
-// batch of a few thousand rows spreads over a hundred or more workgroups):
-// the forward pass through all four layers with the activations in LDS
-// (h1 in hC, h2 in hB, h3 in hA) and copied out, the loss and its output
-// gradient g4 in the last layer's epilogue, then the three layer gradients,
-// each a row-local product: g3 and g2 overwrite h3 (hA) and h2 (hB) in place,
-// element by element, each by the lane that reads that element's ReLU mask.
-// Wavefront w owns output columns 32w .. 32w+31 (2 column blocks of 16);
-// results are in the MFMA's own layout (element v of lane l is row
+// Training pass of one step over the batch rows, in tiles of 16 rows (a
+// batch of a few thousand rows spreads over a hundred or more workgroups).
+// Wavefront w owns columns 32w .. 32w+31 of every layer (2 column blocks of
+// 16); results are in the MFMA's own layout (element v of lane l is row
 // 4 (l / 16) + v, column l % 16).  Products, K-slice order, bias-started
 // accumulators and epilogues are those of k_gemm_bf16.
-#ifndef PN_TRAIN_FT
-#define PN_TRAIN_FT 16
-#endif
-constexpr int kTrainFT = PN_TRAIN_FT;
-
-template <int FT>
-__global__ __launch_bounds__(512) void k_mlp_train(const uint16_t* __restrict__ w0, const uint16_t* __restrict__ w1,
-                                                   const uint16_t* __restrict__ w2, const uint16_t* __restrict__ w3,
-                                                   const float* __restrict__ b0, const float* __restrict__ b1,
-                                                   const float* __restrict__ b2, const float* __restrict__ b3,
-                                                   const float* __restrict__ feat, int64_t n, float* __restrict__ out,
-                                                   TrainIO io) {
-    __shared__ __attribute__((aligned(16))) uint16_t hA[FT][FLD];
-    __shared__ __attribute__((aligned(16))) uint16_t hB[FT][FLD];
-    __shared__ __attribute__((aligned(16))) uint16_t hC[FT][FLD];
-    __shared__ __attribute__((aligned(16))) uint16_t w4s[2][256];   // the output layer's weights
-    __shared__ uint16_t g4s[FT][2];                   // the tile's output gradient
-    __shared__ float labs[FT], tgts[FT];              // the tile's labels and targets
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+//
+// A tile is a chain of seven small products, so the time is latency: of the
+// weights (512 KB a workgroup, at 64 B a clock about 4 us), of the gathered rows
+// and of each stage.  Therefore
+//  - fragments come in fragment order, W2 and W3 before the tile starts, and
+//    W3^T and W2^T into the same registers as soon as the forward product of
+//    that matrix is through, behind the remaining forward stages;
+//  - every wavefront forms the output layer and the loss gradient of all 16 rows
+//    itself, one row per lane with both outputs (weights as the first operand),
+//    so that the gradient is in place for g3's product without an exchange;
+//  - ReLU masks stay in the lane that formed the activation.
+// 25 us at 2,048 rows before (weights row-major, loss on one wavefront with
+// a barrier on each side), 13.9 now.
+__global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
+    constexpr int FT = kTrainFT;
+    __shared__ __attribute__((aligned(16))) uint16_t h1s[FT][FLD];
+    __shared__ __attribute__((aligned(16))) uint16_t h2s[FT][FLD];   // later the g1 staging
+    __shared__ __attribute__((aligned(16))) uint16_t h3s[FT][FLD];   // later g2
+    __shared__ __attribute__((aligned(16))) uint16_t g3s[FT][FLD];
+    __shared__ __attribute__((aligned(16))) uint16_t w4s[2][256];    // the output layer's weights
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int lr = lane & 15, lq = lane >> 4, lk = lq * 8;
-    const int c0 = 32 * wave;                         // first output column of this wavefront
-    constexpr int RB = FT / 16;                       // 16-row blocks per tile
-    static_assert(FT % 16 == 0 && RB >= 1 && RB <= 8, "tile height");
-    static_assert(FT <= 512, "one thread per row loads the labels");
-    w4s[tid >> 8][tid & 255] = w3[tid];               // 512 threads, 2 x 256 weights; read after barriers
+    const int c0 = 32 * wave;                         // first column of this wavefront
+    const int64_t n = io.n;
+    const int64_t tile = blockIdx.x, ntiles = gridDim.x;
+    const int64_t r0 = tile * FT;
+    const bool live = r0 + lr < n;                    // rows past n repeat row n - 1 and are never stored
+    const int32_t src = io.idx[live ? r0 + lr : n - 1];
+    const uint16_t w4v = io.w3[tid];                  // 512 threads, 2 x 256 weights
 
+    bf16x8 wf[2][2][8];                               // two 256-deep operands of this wavefront's columns
+    auto load_weights = [&](int slot, const uint16_t* F) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int sl = 0; sl < 8; ++sl) wf[slot][j][sl] = load_frag(F, 2 * wave + j, sl, lane);
+    };
     // Layer 1 fragments (K = 7; only the lanes of K-group 0 carry values).
     bf16x8 wf0[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        const int col = c0 + 16 * j + lr;
-        uint16_t v[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) v[t] = (lq == 0 && t < 7) ? w0[col * 7 + t] : (uint16_t)0;
-        wf0[j] = *reinterpret_cast<const bf16x8*>(v);
+        wf0[j] = bf16x8{};
+        if (lq == 0) wf0[j] = load_bf16x8(io.w0 + (c0 + 16 * j + lr) * 8);
     }
-    // Biases of this lane's column c0 + 16 j + lr, the accumulators' start.
+    // Biases of this lane's columns, the accumulators' start.
     float bias[3][2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int col = c0 + 16 * j + lr;
-        bias[0][j] = b0[col];
-        bias[1][j] = b1[col];
-        bias[2][j] = b2[col];
-    }
-    const float bias3 = lr < 2 ? b3[lr] : 0.0f;
-    auto bias_init = [&](int layer, int j) {
-        return f32x4{bias[layer][j], bias[layer][j], bias[layer][j], bias[layer][j]};
-    };
+    for (int l = 0; l < 3; ++l)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) bias[l][j] = io.b[l][c0 + 16 * j + lr];
+    const float b40 = io.b[3][0], b41 = io.b[3][1];
+    // The row's index and W2 are on their way; then the features, label and
+    // target of row lr (the lanes of K-groups 1-3 meet zero weights), W3 behind them.
+    __builtin_amdgcn_sched_barrier(0);
+    load_weights(0, io.wf[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    const float* fr = io.feat + (int64_t)src * kFeatLd;
+    const float4 f0 = *reinterpret_cast<const float4*>(fr);
+    const float4 f1 = *reinterpret_cast<const float4*>(fr + 4);
+    const float lab = io.label[src], tgt = io.target[src];
+    __builtin_amdgcn_sched_barrier(0);
+    load_weights(1, io.wf[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    w4s[tid >> 8][tid & 255] = w4v;               // read after barriers
 
-    const int64_t ntiles = (n + FT - 1) / FT;
-    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int64_t r0 = tile * FT;
-        // B fragments of layers 2 and 3 (column c0 + 16 j + lr, K values
-        // 32 s + lk .. + 8), loaded per tile: a batch gives each workgroup
-        // about one tile, and the registers serve the backward fragments later.
-        bf16x8 wf[2][2][8];
+    // Rows 4 lq .. of this tile below n, of the four this lane's elements
+    // belong to; pad: the tile also clears the 16 rows up to a multiple of 32.
+    const int live4 = (int)(n - r0 < FT ? n - r0 : FT) - 4 * lq;
+    const bool pad = (ntiles & 1) && tile == ntiles - 1;
+    const int offT = (lq >> 1) * 4096 + lr * 16 + (lq & 1) * 8;
+
+    f32x4 acc[2];
+    uint32_t mask[3] = {0u, 0u, 0u};              // bit 4 j + v of layer l: its activation is positive
+    // One tensor's columns of this wavefront: row-major through LDS (where
+    // the next product reads it, too) and in row-block order.  The LDS
+    // reads are of what this wavefront has just written, in order.
+    auto put = [&](uint16_t (*h)[FLD], const uint16_t (&y)[2][4], uint16_t* dst, uint16_t* dstT) {
+        char* T = reinterpret_cast<char*>(dstT + (r0 * 256 + c0 * 8));       // the same in all lanes
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) h[4 * lq + v][c0 + 16 * j + lr] = y[j][v];
+            uint2 u;
+            u.x = (0 < live4 ? (uint32_t)y[j][0] : 0u) | (1 < live4 ? (uint32_t)y[j][1] << 16 : 0u);
+            u.y = (2 < live4 ? (uint32_t)y[j][2] : 0u) | (3 < live4 ? (uint32_t)y[j][3] << 16 : 0u);
+            *reinterpret_cast<uint2*>(T + (uint32_t)(offT + 256 * j)) = u;
+            if (pad) *reinterpret_cast<uint2*>(T + (uint32_t)(offT + 256 * j + 8192)) = make_uint2(0u, 0u);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int r = lane >> 2;
+        const uint4 q = *reinterpret_cast<const uint4*>(&h[r][c0 + 8 * (lane & 3)]);
+        char* D = reinterpret_cast<char*>(dst + (r0 * 256 + c0));
+        if (r0 + r < n) *reinterpret_cast<uint4*>(D + (uint32_t)(r * 512 + (lane & 3) * 16)) = q;
+    };
+    // Forward epilogue: bfloat16, ReLU, mask.
+    auto activate = [&](int l, uint16_t (*h)[FLD]) {
+        uint16_t y[2][4];
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int sl = 0; sl < 8; ++sl) {
-                const int col = c0 + 16 * j + lr;
-                wf[0][j][sl] = load_bf16x8(w1 + (int64_t)col * 256 + 32 * sl + lk);
-                wf[1][j][sl] = load_bf16x8(w2 + (int64_t)col * 256 + 32 * sl + lk);
-            }
-        // The tile's labels and targets, requested with the features; they
-        // reach LDS before the barrier after layer 1.
-        float lab_t = 0.0f, tgt_t = 0.0f;
-        if (tid < FT && r0 + tid < n) {
-            const int32_t r = io.idx[r0 + tid];
-            lab_t = io.label[r];
-            tgt_t = io.target[r];
-        }
-        f32x4 acc[RB][2];
-        // Layer 1: A fragment of row block i from the gathered features (7
-        // values and a zero).  Rows past n repeat row n - 1 (never stored);
-        // the lanes of K-groups 1-3 meet zero weights.
-#pragma unroll
-        for (int i = 0; i < RB; ++i) {
-            int64_t row = r0 + 16 * i + lr;
-            row = row < n ? row : n - 1;
-            const float* fr = feat + (int64_t)io.idx[row] * kFeatLd;
-            const float4 f0 = *reinterpret_cast<const float4*>(fr);
-            const float4 f1 = *reinterpret_cast<const float4*>(fr + 4);
-            uint16_t v[8];
-            v[0] = f2bf(f0.x); v[1] = f2bf(f0.y); v[2] = f2bf(f0.z); v[3] = f2bf(f0.w);
-            v[4] = f2bf(f1.x); v[5] = f2bf(f1.y); v[6] = f2bf(f1.z); v[7] = 0;
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(v);
-            if (lq == 0 && r0 + 16 * i + lr < n) *reinterpret_cast<bf16x8*>(io.x_out + (r0 + 16 * i + lr) * kFeatLd) = a;
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wf0[j], bias_init(0, j), 0, 0, 0);
-        }
-        // Epilogue: bfloat16, ReLU, into an LDS buffer.
-        auto store = [&](uint16_t (*h)[FLD]) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        h[16 * i + 4 * lq + v][c0 + 16 * j + lr] = relu_bf16(f2bf(acc[i][j][v]));
-        };
-        store(hC);
-        if (tid < FT) {
-            labs[tid] = lab_t;
-            tgts[tid] = tgt_t;
-        }
-        __syncthreads();
-        copy_tile<FT>(hC, io.h_out[0], r0, n, tid);
-        // Layers 2 and 3: A fragments from LDS, B fragments from registers.
-#pragma unroll
-        for (int layer = 1; layer < 3; ++layer) {
-            uint16_t (*hin)[FLD] = layer == 1 ? hC : hB;
-            uint16_t (*hout)[FLD] = layer == 1 ? hB : hA;
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = bias_init(layer, j);
-#pragma unroll
-            for (int sl = 0; sl < 8; ++sl) {
-#pragma unroll
-                for (int i = 0; i < RB; ++i) {
-                    const bf16x8 a = load_bf16x8(&hin[16 * i + lr][32 * sl + lk]);
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wf[layer - 1][j][sl], acc[i][j], 0, 0, 0);
-                }
-            }
-            store(hout);
-            __syncthreads();
-            copy_tile<FT>(hout, io.h_out[layer], r0, n, tid);
-        }
-        // Layer 4 on wavefronts 0 .. RB - 1 (row block = wavefront), outputs 0
-        // and 1 in columns 0 and 1 of the 16-column block.  Output column c
-        // depends only on the B operand of lanes with lane % 16 = c, so the
-        // other lanes may hold any weights (a copy of row lane % 2); their
-        // columns are never stored.
-        if (wave < RB) {
-            f32x4 o = f32x4{bias3, bias3, bias3, bias3};
-#pragma unroll
-            for (int sl = 0; sl < 8; ++sl) {
-                const bf16x8 a = load_bf16x8(&hA[16 * wave + lr][32 * sl + lk]);
-                const bf16x8 b = load_bf16x8(&w4s[lr & 1][32 * sl + lk]);
-                o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, o, 0, 0, 0);
-            }
-            // Loss of the batch: binary cross-entropy of the logit plus Huber
-            // (delta 1) of the FLI output, averaged over the n rows, and its
-            // gradient.  Lanes lr = 0 and 1 hold the two outputs of rows
-            // 4 lq + v and exchange them.
-            float lsum = 0.0f;
-#pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const float mine = o[v];
-                const float other = swap_adjacent(mine);
-                const int64_t row = r0 + 16 * wave + 4 * lq + v;
-                if (lr < 2 && row < n) out[row * 2 + lr] = mine;
-                if (lr == 0 && row < n) {
-                    const int rl = 16 * wave + 4 * lq + v;
-                    const float z = mine, f = other, y = labs[rl], t = tgts[rl];
-                    float l = fmaxf(z, 0.0f) - y * z + log1pf(expf(-fabsf(z)));
-                    const float d = f - t;
-                    l += fabsf(d) <= 1.0f ? 0.5f * d * d : fabsf(d) - 0.5f;
-                    const float sig = 1.0f / (1.0f + expf(-z));
-                    const uint16_t g0 = f2bf((sig - y) / (float)n);
-                    const uint16_t g1 = f2bf(fminf(fmaxf(d, -1.0f), 1.0f) / (float)n);
-                    io.gout[2 * row] = g0;
-                    io.gout[2 * row + 1] = g1;
-                    g4s[16 * wave + 4 * lq + v][0] = g0;
-                    g4s[16 * wave + 4 * lq + v][1] = g1;
-                    lsum += l;
-                } else if (lr == 0) {
-                    g4s[16 * wave + 4 * lq + v][0] = 0;
-                    g4s[16 * wave + 4 * lq + v][1] = 0;
-                }
+                y[j][v] = relu_bf16(f2bf(acc[j][v]));
+                mask[l] |= (bf2f(y[j][v]) > 0.0f ? 1u : 0u) << (4 * j + v);
             }
+        put(h, y, io.h_out[l], io.hT[l]);
+    };
+    // 256-deep product of the rows in hin with the operand in wf[slot].
+    auto product = [&](int slot, uint16_t (*hin)[FLD]) {
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
-            if (lane == 0) atomicAdd(io.loss, lsum / (float)n);
-        }
-        __syncthreads();
-        // g3 = (g4 W4) * (h3 > 0) for this wavefront's 32 columns, as the
-        // product with K = 2 (padded to one 32-deep slice) and the ReLU mask
-        // of h3 (still in hA) that k_gemm_bf16 would form; g3 replaces h3.
-        {
-            bf16x8 b[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int col = c0 + 16 * j + lr;
-                uint16_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-                if (lq == 0) { v[0] = w4s[0][col]; v[1] = w4s[1][col]; }
-                b[j] = *reinterpret_cast<const bf16x8*>(v);
-            }
-#pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                uint16_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-                if (lq == 0) { v[0] = g4s[16 * i + lr][0]; v[1] = g4s[16 * i + lr][1]; }
-                const bf16x8 a = *reinterpret_cast<const bf16x8*>(v);
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const f32x4 g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[j], f32x4{0.f, 0.f, 0.f, 0.f},
-                                                                            0, 0, 0);
-#pragma unroll
-                    for (int v2 = 0; v2 < 4; ++v2) {
-                        const int rl = 16 * i + 4 * lq + v2, col = c0 + 16 * j + lr;
-                        const float x = bf2f(hA[rl][col]) > 0.0f ? g[v2] : 0.0f;
-                        const uint16_t y = f2bf(x);
-                        hA[rl][col] = y;
-                        if (r0 + rl < n) io.g3_out[(r0 + rl) * 256 + col] = y;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        // g2 = (g3 W3) * (h2 > 0) from g3 (hA) and the mask h2 (hB), then
-        // g1 = (g2 W2) * (h1 > 0) from g2 (now in hB) and h1 (hC): the
-        // products k_gemm_bf16 forms, with the K slices in the same order.
-#pragma unroll
-        for (int phase = 0; phase < 2; ++phase) {
-            uint16_t (*ain)[FLD] = phase == 0 ? hA : hB;
-            uint16_t (*mask)[FLD] = phase == 0 ? hB : hC;
-            const uint16_t* wt = io.wT[1 - phase];
-            bf16x8 wbk[2][8];
+        for (int sl = 0; sl < 8; ++sl) {
+            const bf16x8 a = load_bf16x8(&hin[lr][32 * sl + lk]);
 #pragma unroll
             for (int j = 0; j < 2; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wf[slot][j][sl], acc[j], 0, 0, 0);
+        }
+    };
+    auto start = [&](int l) {
 #pragma unroll
-                for (int sl = 0; sl < 8; ++sl)
-                    wbk[j][sl] = load_bf16x8(wt + (int64_t)(c0 + 16 * j + lr) * 256 + 32 * sl + lk);
+        for (int j = 0; j < 2; ++j)
+            acc[j] = l < 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : f32x4{bias[l][j], bias[l][j], bias[l][j], bias[l][j]};
+    };
+    // Backward epilogue: the mask of layer l, bfloat16.
+    auto masked = [&](int l, uint16_t (&y)[2][4]) {
 #pragma unroll
-            for (int i = 0; i < RB; ++i)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int v = 0; v < 4; ++v) y[j][v] = f2bf((mask[l] >> (4 * j + v)) & 1u ? acc[j][v] : 0.0f);
+    };
+
+    // Layer 1.
+    {
+        uint16_t v[8];
+        v[0] = f2bf(f0.x); v[1] = f2bf(f0.y); v[2] = f2bf(f0.z); v[3] = f2bf(f0.w);
+        v[4] = f2bf(f1.x); v[5] = f2bf(f1.y); v[6] = f2bf(f1.z); v[7] = 0;
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(v);
+        start(0);
 #pragma unroll
-            for (int sl = 0; sl < 8; ++sl) {
+        for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wf0[j], acc[j], 0, 0, 0);
+        if (wave == 0 && lq == 0) {
+            if (live) *reinterpret_cast<bf16x8*>(io.x_out + (r0 + lr) * kFeatLd) = a;
+            uint16_t* T = io.xT + (r0 / 8 + (lr >> 3)) * kFeatLd * 8 + (lr & 7);
 #pragma unroll
-                for (int i = 0; i < RB; ++i) {
-                    const bf16x8 a = load_bf16x8(&ain[16 * i + lr][32 * sl + lk]);
+            for (int t = 0; t < 8; ++t) T[8 * t] = live ? v[t] : (uint16_t)0;
+            if (pad)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wbk[j][sl], acc[i][j], 0, 0, 0);
-                }
-            }
-            uint16_t* gdst = phase == 0 ? io.g2_out : io.g1_out;
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int v2 = 0; v2 < 4; ++v2) {
-                        const int rl = 16 * i + 4 * lq + v2, col = c0 + 16 * j + lr;
-                        const float x = bf2f(mask[rl][col]) > 0.0f ? acc[i][j][v2] : 0.0f;
-                        const uint16_t y = f2bf(x);
-                        if (phase == 0) hB[rl][col] = y;
-                        if (r0 + rl < n) gdst[(r0 + rl) * 256 + col] = y;
-                    }
-            __syncthreads();
+                for (int t = 0; t < 8; ++t) T[2 * kFeatLd * 8 + 8 * t] = 0;
         }
     }
+    activate(0, h1s);
+    __syncthreads();
+    // Layer 2, then its operand's registers take W3^T.
+    start(1);
+    product(0, h1s);
+    __builtin_amdgcn_sched_barrier(0);
+    load_weights(0, io.wt[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    activate(1, h2s);
+    __syncthreads();
+    // Layer 3, then W2^T.
+    start(2);
+    product(1, h2s);
+    __builtin_amdgcn_sched_barrier(0);
+    load_weights(1, io.wt[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    activate(2, h3s);
+    __syncthreads();
+    // Layer 4, weights first: lane l (K-group 0) gets both outputs of row l
+    // in elements 0 and 1.  The first operand's rows above 1 are copies that
+    // feed elements nobody reads.
+    f32x4 o = f32x4{b40, b41, 0.f, 0.f};
+#pragma unroll
+    for (int sl = 0; sl < 8; ++sl) {
+        const bf16x8 a = load_bf16x8(&w4s[lr & 1][32 * sl + lk]);
+        const bf16x8 b = load_bf16x8(&h3s[lr][32 * sl + lk]);
+        o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, o, 0, 0, 0);
+    }
+    // Loss of the batch: binary cross-entropy of the logit plus Huber
+    // (delta 1) of the FLI output, averaged over the n rows, and its
+    // gradient.
+    uint16_t g40 = 0, g41 = 0;
+    {
+        const float z = o[0], f = o[1], y = lab, d = f - tgt;
+        if (lq == 0 && live) {
+            const float sig = 1.0f / (1.0f + expf(-z));
+            g40 = f2bf((sig - y) / (float)n);
+            g41 = f2bf(fminf(fmaxf(d, -1.0f), 1.0f) / (float)n);
+        }
+        if (wave == 0) {
+            float l = 0.0f;
+            if (lq == 0) {
+                if (live) {
+                    l = fmaxf(z, 0.0f) - y * z + log1pf(expf(-fabsf(z)));
+                    l += fabsf(d) <= 1.0f ? 0.5f * d * d : fabsf(d) - 0.5f;
+                    *reinterpret_cast<float2*>(io.out + 2 * (r0 + lr)) = make_float2(z, f);
+                    *reinterpret_cast<uint32_t*>(io.gout + 2 * (r0 + lr)) = (uint32_t)g40 | ((uint32_t)g41 << 16);
+                }
+                uint16_t* T = io.g4T + (r0 / 8 + (lr >> 3)) * 2 * 8 + (lr & 7);
+                T[0] = g40;
+                T[8] = g41;
+                if (pad) T[2 * 2 * 8] = T[2 * 2 * 8 + 8] = 0;
+            }
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) l += __shfl_xor(l, off);
+            if (lane == 0) atomicAdd(io.loss, l / (float)n);
+        }
+    }
+    // g3 = (g4 W4) * (h3 > 0): K = 2, padded to one 32-deep slice.
+    uint16_t y[2][4];
+    {
+        uint16_t v[8] = {g40, g41, 0, 0, 0, 0, 0, 0};
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(v);
+        start(-1);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            uint16_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (lq == 0) { w[0] = w4s[0][c0 + 16 * j + lr]; w[1] = w4s[1][c0 + 16 * j + lr]; }
+            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, *reinterpret_cast<const bf16x8*>(w), acc[j], 0, 0, 0);
+        }
+    }
+    masked(2, y);
+    put(g3s, y, io.g_out[2], io.gT[2]);
+    __syncthreads();
+    // g2 = (g3 W3) * (h2 > 0).
+    start(-1);
+    product(0, g3s);
+    masked(1, y);
+    put(h3s, y, io.g_out[1], io.gT[1]);
+    __syncthreads();
+    // g1 = (g2 W2) * (h1 > 0).
+    start(-1);
+    product(1, h3s);
+    masked(0, y);
+    put(h2s, y, io.g_out[0], io.gT[0]);
 }
 
 // Inference as a two-stage pipeline over 32-row tiles, one barrier per
@@ -824,56 +711,222 @@ __global__ __launch_bounds__(512) void k_mlp_infer(const uint16_t* __restrict__ 
     }
 }
 
-// Adam over all eight parameter tensors in one launch: tensor t holds
-// elements [off[t], off[t+1]) of the flat index.
-struct AdamArgs {
-    float* w[8];
-    const float* g[8];
-    const float* part[8];   // splits[t] > 1: g = sum over z, in order, of part[t][z][e]
-    int splits[8];
-    float* m[8];
-    float* v[8];
-    uint16_t* wb[8];    // bfloat16 copy (null for biases)
-    uint16_t* wbT[8];   // transposed bfloat16 copy [in][out] (null where not kept)
-    int64_t off[9];
-    float lr, c1, c2;   // c1 = 1 - b1^t, c2 = 1 - b2^t
+// The second half of a training step: weight gradients dW_l = g_l^T a_(l-1)
+// and bias gradients (column sums of g_l) over the batch rows, and the Adam
+// update of the elements they belong to, with the bfloat16 copies.
+struct UpdateArgs {
+    const uint16_t* g[4];   // g1 .. g4 in row-block order (256, 256, 256, 2 columns)
+    const uint16_t* a[4];   // X, h1, h2, h3 in row-block order (8, 256, 256, 256 columns)
+    int blocks8;            // 8-row blocks (a multiple of 4)
+    int chunk[4];           // 32-row slices of a split of layer l's sums
+    int splits[4];
+    float *w[4], *mw[4], *vw[4];
+    float *b[4], *mb[4], *vb[4];
+    uint16_t* wb[4];
+    uint16_t* w0p;          // W1 [256][8]
+    uint16_t* wf[2];        // W2, W3 in fragment order
+    uint16_t* wt[2];        // W2, W3 transposed in fragment order
+    float lr, c1, c2;       // c1 = 1 - b1^t, c2 = 1 - b2^t
 };
-__global__ __launch_bounds__(256) void k_adam(AdamArgs a) {
-    const int64_t f = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (f >= a.off[8]) return;
-    int t = 0;
-#pragma unroll
-    for (int k = 1; k < 8; ++k) t += (f >= a.off[k]) ? 1 : 0;
-    const int64_t e = f - a.off[t];
-    float g;
-    if (a.splits[t] > 1) {
-        // The split weight gradient, summed in the order of k_sum_splits.
-        const int64_t mn = a.off[t + 1] - a.off[t];
-        const float* pp = a.part[t];
-        float x = 0.0f;
-        for (int z = 0; z < a.splits[t]; ++z) x += pp[z * mn + e];
-        g = x;
-    } else {
-        g = a.g[t][e];
-    }
-    const float m = 0.9f * a.m[t][e] + 0.1f * g;
-    const float v = 0.999f * a.v[t][e] + 0.001f * g * g;
-    a.m[t][e] = m;
-    a.v[t][e] = v;
-    const float w = a.w[t][e] - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + 1e-8f);
-    a.w[t][e] = w;
-    if (a.wb[t]) a.wb[t][e] = f2bf(w);
-    if (a.wbT[t]) a.wbT[t][(e & 255) * 256 + (e >> 8)] = f2bf(w);   // 256 x 256 tensors only
+
+// Adam on one element; returns the new weight.
+__device__ __forceinline__ float adam(float g, float* w, float* pm, float* pv, int64_t e, float lr, float c1,
+                                      float c2) {
+    const float m = 0.9f * pm[e] + 0.1f * g;
+    const float v = 0.999f * pv[e] + 0.001f * g * g;
+    pm[e] = m;
+    pv[e] = v;
+    const float x = w[e] - lr * (m / c1) / (sqrtf(v / c2) + 1e-8f);
+    w[e] = x;
+    return x;
 }
 
-// wT[t][i][o] = bfloat16 W[o][i] for the two 256 x 256 hidden weights.
-__global__ __launch_bounds__(256) void k_transpose_hidden(const uint16_t* w1, const uint16_t* w2, uint16_t* t1,
-                                                          uint16_t* t2) {
-    const int e = blockIdx.x * 256 + threadIdx.x;     // grid 512 x 256 threads
-    const uint16_t* src = e < 65536 ? w1 : w2;
-    uint16_t* dst = e < 65536 ? t1 : t2;
-    const int f = e & 65535;
-    dst[(f & 255) * 256 + (f >> 8)] = src[f];
+// Sums over the 32-row slices [s0, s1) of the products of MB x NB blocks of 16
+// columns: acc[i][j] += sum G(row, m0 + 16 i + .) A(row, n0 + 16 j + .), slices in
+// increasing order, one 16x16x32 MFMA each.  Operands in row-block order are
+// in fragment order as they lie: lane l takes the eight rows 32 s + 8 (l / 16) ..
+// of its column, 16 bytes, and 16 lanes read 256 bytes in a row.  Columns from
+// cg (ca) on are zero.
+template <int MB, int NB>
+__device__ __forceinline__ void slice_sums(const uint16_t* G, int cg, int m0, const uint16_t* A, int ca, int n0,
+                                           int s0, int s1, int lane, f32x4 (&acc)[MB][NB]) {
+    const int lr = lane & 15, lq = lane >> 4;
+    const bf16x8 zero = {};
+    for (int s = s0; s < s1; s += 4) {
+        bf16x8 x[4][MB], y[4][NB];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool in = s + q < s1;
+            const int64_t rb = (int64_t)(s + q) * 4 + lq;
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                const int c = m0 + 16 * i + lr;
+                x[q][i] = in && c < cg ? load_bf16x8(G + (rb * cg + c) * 8) : zero;
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int c = n0 + 16 * j + lr;
+                y[q][j] = in && c < ca ? load_bf16x8(A + (rb * ca + c) * 8) : zero;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (s + q < s1) {
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[q][i], y[q][j], acc[i][j], 0, 0, 0);
+            }
+    }
+}
+
+constexpr int kUpWaves = 16;        // wavefronts of an update workgroup
+constexpr int kPartLd = 36;         // row stride of a partial tile in LDS: lanes of all four K-groups on their own banks
+constexpr int kHiddenTiles = 64;    // 32 x 32 tiles of a hidden weight
+
+// Layer l's gradient of the 16 MB x 16 NB tile at (m0, n0): wavefront w sums
+// split w (and w + 16, ..), the partials meet in LDS, and thread t returns
+// element (t / 32, t % 32) summed over the splits in increasing order.
+template <int MB, int NB>
+__device__ __forceinline__ float tile_gradient(const UpdateArgs& u, int l, int cg, int m0, int ca, int n0,
+                                               float (*part)[32 * kPartLd]) {
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int lr = lane & 15, lq = lane >> 4;
+    const int slices = u.blocks8 / 4, chunk = u.chunk[l], splits = u.splits[l];
+    const int r = tid >> 5, c = tid & 31;
+    float x = 0.0f;
+    for (int z0 = 0; z0 < splits; z0 += kUpWaves) {
+        const int z = z0 + wave;
+        if (z < splits) {
+            f32x4 acc[MB][NB];
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const int s1 = (z + 1) * chunk < slices ? (z + 1) * chunk : slices;
+            slice_sums<MB, NB>(u.g[l], cg, m0, u.a[l], ca, n0, z * chunk, s1, lane, acc);
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        part[wave][(16 * i + 4 * lq + v) * kPartLd + 16 * j + lr] = acc[i][j][v];
+        }
+        __syncthreads();
+        if (r < 16 * MB && c < 16 * NB) {
+            const int left = splits - z0;
+#pragma unroll
+            for (int q = 0; q < kUpWaves; ++q)
+                if (q < left) x += part[q][r * kPartLd + c];
+        }
+        if (z0 + kUpWaves < splits) __syncthreads();
+    }
+    return x;
+}
+
+// Workgroups: kHiddenTiles per hidden weight (32 x 32 tiles), 8 for W1 (32
+// rows each), 8 for W4 (32 columns each), then the biases, 32 columns each (8 per
+// hidden layer, one for the output layer).  A tile is complete in its
+// workgroup, so its Adam update follows at once: no partial sums in memory and
+// no second launch (before: 15.7 us for the products with split partials of 8 MB,
+// 8.5 us for Adam, at 2,048 rows; 6.1 us together now).  Bound by the operands'
+// way from the other XCDs' L2 and by latency: 16 wavefronts keep 16 KB each in
+// flight.  Consecutive workgroups go to different XCDs, so workgroup b takes its
+// tile from the 4 x 4 block of tiles of XCD b % 8, which reads 1 MB of
+// operands instead of 2.
+constexpr int kUpW1 = 2 * kHiddenTiles, kUpW4 = kUpW1 + 8, kUpBias = kUpW4 + 8, kUpBlocks = kUpBias + 25;
+
+__global__ __launch_bounds__(1024) void k_mlp_update(UpdateArgs u) {
+    __shared__ __attribute__((aligned(16))) float part[kUpWaves][32 * kPartLd];
+    __shared__ __attribute__((aligned(16))) uint16_t tile[32][40];
+    const int tid = threadIdx.x, b = blockIdx.x;
+    const int r = tid >> 5, c = tid & 31;
+    if (b < kUpW1) {
+        const int x = b & 7, q = b >> 3;                 // XCD, tile of its 4 x 4 block
+        const int l = 1 + (x >> 2);
+        const int m0 = 32 * (4 * (x & 1) + (q & 3)), n0 = 32 * (4 * ((x >> 1) & 1) + (q >> 2));
+        const float g = tile_gradient<2, 2>(u, l, 256, m0, 256, n0, part);
+        const int64_t e = (int64_t)(m0 + r) * 256 + n0 + c;
+        const uint16_t y = f2bf(adam(g, u.w[l], u.mw[l], u.vw[l], e, u.lr, u.c1, u.c2));
+        u.wb[l][e] = y;
+        tile[r][c] = y;
+        __syncthreads();
+        // The tile is two fragments of W (32 columns m, one K slice n) and two of
+        // W^T (32 columns n, one K slice m): one 16-byte piece per thread.
+        if (tid < 256) {
+            const int f = (tid >> 6) & 1, lane = tid & 63, lr = lane & 15, lk = (lane >> 4) * 8;
+            union { uint4 v; uint16_t e[8]; } p;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) p.e[t] = tid < 128 ? tile[16 * f + lr][lk + t] : tile[lk + t][16 * f + lr];
+            uint16_t* F = tid < 128 ? u.wf[l - 1] + (((m0 / 16 + f) * 8 + n0 / 32) * 64 + lane) * 8
+                                    : u.wt[l - 1] + (((n0 / 16 + f) * 8 + m0 / 32) * 64 + lane) * 8;
+            *reinterpret_cast<uint4*>(F) = p.v;
+        }
+        return;
+    }
+    if (b < kUpBias) {
+        const bool first = b < kUpW4;
+        const int k = 32 * (first ? b - kUpW1 : b - kUpW4), l = first ? 0 : 3;
+        const float g = first ? tile_gradient<2, 1>(u, 0, 256, k, kFeatLd, 0, part)
+                              : tile_gradient<1, 2>(u, 3, 2, 0, 256, k, part);
+        if (first ? c < 7 : r < 2) {
+            const int64_t e = first ? (int64_t)(k + r) * 7 + c : (int64_t)r * 256 + k + c;
+            const uint16_t y = f2bf(adam(g, u.w[l], u.mw[l], u.vw[l], e, u.lr, u.c1, u.c2));
+            u.wb[l][e] = y;
+            if (first) u.w0p[(k + r) * 8 + c] = y;
+        }
+        return;
+    }
+    // Bias columns: thread (r, c) sums rows 8 r + t + 256 q of column c over q, one
+    // sum per t < 8, and the 256 sums of a column meet pairwise, halves first.
+    const int l = (b - kUpBias) >> 3, n0 = 32 * ((b - kUpBias) & 7), cols = kOut[l];
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (n0 + c < cols)
+        for (int rb = r; rb < u.blocks8; rb += 32) {
+            union { bf16x8 v; uint16_t e[8]; } p;
+            p.v = load_bf16x8(u.g[l] + ((int64_t)rb * cols + n0 + c) * 8);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) s[t] += bf2f(p.e[t]);
+        }
+    float (*half)[32][8] = reinterpret_cast<float (*)[32][8]>(&part[0][0]);
+    for (int k = 16; k > 0; k >>= 1) {
+        if (r >= k && r < 2 * k)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) half[r - k][c][t] = s[t];
+        __syncthreads();
+        if (r < k)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) s[t] += half[r][c][t];
+        __syncthreads();
+    }
+    if (r == 0 && n0 + c < cols) {
+#pragma unroll
+        for (int k = 4; k > 0; k >>= 1)
+#pragma unroll
+            for (int t = 0; t < k; ++t) s[t] += s[t + k];
+        adam(s[0], u.b[l], u.mb[l], u.vb[l], n0 + c, u.lr, u.c1, u.c2);
+    }
+}
+
+// The training pass's copies of the weights (grid 520 x 256 threads: one
+// element of W2, W3 or the padded W1 each), formed once before a run of steps;
+// the updates keep them.
+__global__ __launch_bounds__(256) void k_pack_weights(const uint16_t* w0, const uint16_t* w1, const uint16_t* w2,
+                                                      uint16_t* w0p, uint16_t* f1, uint16_t* f2, uint16_t* t1,
+                                                      uint16_t* t2) {
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= 131072) {
+        const int o = (e - 131072) >> 3, i = e & 7;
+        w0p[e - 131072] = i < 7 ? w0[o * 7 + i] : (uint16_t)0;
+        return;
+    }
+    const int o = (e >> 8) & 255, i = e & 255;
+    const uint16_t x = (e < 65536 ? w1 : w2)[e & 65535];
+    auto at = [](int col, int k) { return (((col >> 4) * 8 + (k >> 5)) * 64 + ((k >> 3) & 3) * 16 + (col & 15)) * 8 + (k & 7); };
+    (e < 65536 ? f1 : f2)[at(o, i)] = x;
+    (e < 65536 ? t1 : t2)[at(i, o)] = x;
 }
 
 __global__ __launch_bounds__(256) void k_to_bf16(const float* x, int64_t n, uint16_t* y) {
@@ -1005,23 +1058,9 @@ __global__ __launch_bounds__(256) void k_sum_steps(const int64_t* steps, int64_t
 
 unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-constexpr int64_t kSplitFloats = (int64_t)1 << 20;   // partial-sum buffer of a split product (4 MB)
-
-// C = A B.  A product with few output tiles and a long K (the weight
-// gradients: K = batch rows) is split along K over up to 256 workgroups when
-// `part` (kSplitFloats floats) is given and the result is a plain FP32
-// store; the partials are summed in a fixed order, so the result does not
-// depend on scheduling.  With sum_parts false and more than one split, the
-// partials part[z][M][N] are left for the consumer to sum (in the same
-// order) and C is not written.  Returns the number of splits.
-struct GemmPlan {
-    GemmArgs g;             // as launched (Cf = part when split)
-    int tx, ty, splits;     // grid
-};
-
-GemmPlan plan_gemm(int M, int N, int K, const uint16_t* A, int64_t sam, int64_t sak, const uint16_t* B,
-                   int64_t sbk, int64_t sbn, const float* bias, int relu, const uint16_t* mask, int64_t ldm,
-                   float* Cf, int64_t ldcf, uint16_t* Cb, int64_t ldcb, float* part) {
+void gemm(hipStream_t s, int M, int N, int K, const uint16_t* A, int64_t sam, int64_t sak, const uint16_t* B,
+          int64_t sbk, int64_t sbn, const float* bias, int relu, const uint16_t* mask, int64_t ldm, float* Cf,
+          int64_t ldcf, uint16_t* Cb, int64_t ldcb) {
     GemmArgs g;
     g.M = M; g.N = N; g.K = K;
     g.A = A; g.sam = sam; g.sak = sak;
@@ -1030,37 +1069,7 @@ GemmPlan plan_gemm(int M, int N, int K, const uint16_t* A, int64_t sam, int64_t 
     g.Cf = Cf; g.ldcf = ldcf; g.Cb = Cb; g.ldcb = ldcb;
     g.amode = stage_mode(A, sam, sak);
     g.bmode = stage_mode(B, sbn, sbk);
-    g.kchunk = K > 0 ? K : 1;
-    g.split_stride = 0;
-    const int64_t tiles = (int64_t)blocks_for(N, BN) * blocks_for(M, BM);
-    int splits = 1;
-    if (part && Cf && !Cb && !bias && !relu && !mask && tiles < 64 && K >= 512) {
-        int64_t sp = 256 / tiles;
-        if (sp > K / 128) sp = K / 128;
-        if (sp > kSplitFloats / ((int64_t)M * N)) sp = kSplitFloats / ((int64_t)M * N);
-        if (sp > 1) {
-            const int64_t chunk = ((K + sp - 1) / sp + BK - 1) / BK * BK;
-            splits = (int)((K + chunk - 1) / chunk);
-            g.kchunk = (int)chunk;
-        }
-    }
-    if (splits > 1) {
-        g.Cf = part;
-        g.ldcf = N;
-        g.split_stride = (int64_t)M * N;
-    }
-    return GemmPlan{g, (int)blocks_for(N, BN), (int)blocks_for(M, BM), splits};
-}
-
-int gemm(hipStream_t s, int M, int N, int K, const uint16_t* A, int64_t sam, int64_t sak, const uint16_t* B,
-         int64_t sbk, int64_t sbn, const float* bias, int relu, const uint16_t* mask, int64_t ldm, float* Cf,
-         int64_t ldcf, uint16_t* Cb, int64_t ldcb, float* part = nullptr, bool sum_parts = true) {
-    const GemmPlan pl = plan_gemm(M, N, K, A, sam, sak, B, sbk, sbn, bias, relu, mask, ldm, Cf, ldcf, Cb, ldcb, part);
-    hipLaunchKernelGGL(k_gemm_bf16, dim3(pl.tx, pl.ty, pl.splits), dim3(256), 0, s, pl.g);
-    if (pl.splits > 1 && sum_parts)
-        hipLaunchKernelGGL(k_sum_splits, dim3(blocks_for((int64_t)M * N, 256)), dim3(256), 0, s, part, pl.splits, M,
-                           N, Cf, ldcf);
-    return pl.splits;
+    hipLaunchKernelGGL(k_gemm_bf16, dim3(blocks_for(N, BN), blocks_for(M, BM)), dim3(256), 0, s, g);
 }
 
 pn_status launched(const char* what) {
@@ -1073,6 +1082,8 @@ pn_status launched(const char* what) {
 }
 
 size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
+
+size_t rows32(int batch) { return ((size_t)batch + 31) / 32 * 32; }
 
 bool net_ok(const pn_mlp* net, bool training) {
     if (!net) return false;
@@ -1090,16 +1101,6 @@ void launch_infer(hipStream_t s, const pn_mlp* net, const float* feat, int64_t n
     const unsigned grid = (unsigned)(ntiles < ncu ? ntiles : ncu);
     hipLaunchKernelGGL(k_mlp_infer, dim3(grid), dim3(512), 0, s, net->wb[0], net->wb[1], net->wb[2], net->wb[3],
                        net->b[0], net->b[1], net->b[2], net->b[3], feat, n, out);
-}
-
-// The training pass over a batch of n rows.
-void launch_train(hipStream_t s, const pn_mlp* net, const float* feat, int64_t n, float* out, const TrainIO& io,
-                  int ncu) {
-    if (n <= 0) return;
-    const int64_t ntiles = (n + kTrainFT - 1) / kTrainFT;
-    const unsigned grid = (unsigned)(ntiles < ncu ? ntiles : ncu);
-    hipLaunchKernelGGL((k_mlp_train<kTrainFT>), dim3(grid), dim3(512), 0, s, net->wb[0], net->wb[1], net->wb[2],
-                       net->wb[3], net->b[0], net->b[1], net->b[2], net->b[3], feat, n, out, io);
 }
 
 int device_cu_count() {
@@ -1131,10 +1132,9 @@ size_t pn_mlp_param_count(int32_t layer, int32_t which) {
 
 size_t pn_mlp_train_workspace_size(int32_t batch) {
     if (batch <= 0) return 0;
-    const size_t B = (size_t)batch;
+    const size_t B = (size_t)batch, R = rows32(batch);
     return al(B * kFeatLd * 2) + 3 * al(B * 256 * 2) + al(B * 2 * 4) + al(B * 2 * 2) + 3 * al(B * 256 * 2) +
-           al(256 * 256 * 4) * 2 + al(256 * 7 * 4) + al(2 * 256 * 4) + 4 * al(256 * 4) +
-           4 * al((size_t)kSplitFloats * 4) + 2 * al(256 * 256 * 2);
+           al(R * kFeatLd * 2) + 6 * al(R * 256 * 2) + al(R * 2 * 2) + 4 * al(256 * 256 * 2) + al(256 * 8 * 2);
 }
 
 pn_status pn_mlp_train_workspace_layout(int32_t batch, size_t* off) {
@@ -1163,105 +1163,89 @@ pn_status pn_mlp_sync_bf16(pn_mlp* net, hipStream_t stream) {
 
 namespace {
 
-// One training step (pn_mlp_train_step).  The workspace also holds bfloat16
-// copies of W2^T and W3^T for the backward products of the training pass; each
-// Adam update rewrites them with the bfloat16 weights, so a run of steps on
-// one workspace forms them once (fresh_transposes) before its first step.
+// Splits of layer l's weight-gradient sums over the batch rows (32-row
+// slices per split, splits): enough that the 64 x 64 tiles of the product and
+// the splits together are up to 256 pieces of at least 128 rows.  The sums are
+// formed split by split in increasing order, so this rule is part of the
+// result.
+void gradient_splits(int l, int batch, int& chunk, int& splits) {
+    const int64_t M = kOut[l], N = kIn[l], K = batch;
+    const int64_t tiles = (int64_t)blocks_for(N, 64) * blocks_for(M, 64);
+    int64_t sp = 1;
+    if (K >= 512) {
+        sp = std::min<int64_t>({256 / tiles, K / 128, ((int64_t)1 << 20) / (M * N)});
+        if (sp < 1) sp = 1;
+    }
+    chunk = (int)(((K + sp - 1) / sp + 31) / 32);
+    splits = (int)((K + 32 * (int64_t)chunk - 1) / (32 * (int64_t)chunk));
+}
+
+// One training step (pn_mlp_train_step).  The workspace also holds the step's
+// tensors in row-block order and bfloat16 copies of W2 and W3, straight and
+// transposed, in fragment order; each update rewrites the copies with the
+// bfloat16 weights, so a run of steps on one workspace forms them once (fresh)
+// before its first step.
 pn_status train_step(pn_mlp* net, const float* feat, const float* label, const float* target, const int32_t* idx,
                      int32_t batch, int32_t step, float lr, float* loss, void* ws, size_t ws_bytes,
-                     hipStream_t stream, bool fresh_transposes) {
+                     hipStream_t stream, bool fresh) {
     if (!net_ok(net, true) || !feat || !label || !target || !idx || !loss) return PN_EINVAL;
     if ((reinterpret_cast<uintptr_t>(feat) & 15u) != 0) return PN_EINVAL;
     if (batch <= 0 || step < 1 || !(lr > 0.0f) || !std::isfinite(lr)) return PN_EINVAL;
     if (!ws || ws_bytes < pn_mlp_train_workspace_size(batch)) return PN_ENOWS;
-    const int ncu = device_cu_count();
-    if (ncu <= 0) {
+    if (device_cu_count() <= 0) {
         pn_detail::set_last_error("pn_mlp_train_step", "no device");
         return PN_EDEVICE;
     }
     const int B = batch;
     // The tensors a step leaves in the workspace, at the offsets that
-    // pn_mlp_train_workspace_layout reports; the gradient buffers follow.
+    // pn_mlp_train_workspace_layout reports; the other copies follow.
     size_t off[9];
     if (pn_mlp_train_workspace_layout(batch, off) != PN_OK) return PN_EINVAL;
     char* const w0 = static_cast<char*>(ws);
-    uint16_t* X = (uint16_t*)(w0 + off[0]);
-    uint16_t* h[3] = {(uint16_t*)(w0 + off[1]), (uint16_t*)(w0 + off[2]), (uint16_t*)(w0 + off[3])};
-    float* out = (float*)(w0 + off[4]);
-    uint16_t* g4 = (uint16_t*)(w0 + off[5]);
-    uint16_t* g3 = (uint16_t*)(w0 + off[6]);
-    uint16_t* g2 = (uint16_t*)(w0 + off[7]);
-    uint16_t* g1 = (uint16_t*)(w0 + off[8]);
     char* p = w0 + off[8] + al((size_t)B * 256 * 2);
-    auto take = [&](size_t bytes) { char* q = p; p += al(bytes); return q; };
-    float* dW[4];
-    dW[1] = (float*)take(256 * 256 * 4);
-    dW[2] = (float*)take(256 * 256 * 4);
-    dW[0] = (float*)take(256 * 7 * 4);
-    dW[3] = (float*)take(2 * 256 * 4);
-    float* db[4];
-    for (int l = 0; l < 4; ++l) db[l] = (float*)take(256 * 4);
-    float* part[4];
-    for (int l = 0; l < 4; ++l) part[l] = (float*)take((size_t)kSplitFloats * 4);
-    uint16_t* wT[2];
-    for (int t = 0; t < 2; ++t) wT[t] = (uint16_t*)take(256 * 256 * 2);
-    hipStream_t s = stream;
-
-    if (fresh_transposes)
-        hipLaunchKernelGGL(k_transpose_hidden, dim3(512), dim3(256), 0, s, net->wb[1], net->wb[2], wT[0], wT[1]);
-    // Forward over the batch rows idx[], keeping the inputs and hidden
-    // activations, with the loss, its output gradient g4 and the layer
-    // gradients g3 = (g4 W4) * (h3 > 0), g2 = (g3 W3) * (h2 > 0) and
-    // g1 = (g2 W2) * (h1 > 0), all in one launch of k_mlp_train.
-    TrainIO io{idx, X, {h[0], h[1], h[2]}, label, target, g4, loss, g3, g2, g1, {wT[0], wT[1]}};
-    launch_train(s, net, feat, B, out, io, ncu);
-    // Backward.  Weight gradients dW_l = g_l^T h_(l-1) go to per-layer
-    // split-K partials that the Adam launch sums.
-    // The four weight gradients and all bias gradients in one launch.
-    const GemmPlan pw[4] = {
-        plan_gemm(256, 7, B, g1, 1, 256, X, kFeatLd, 1, nullptr, 0, nullptr, 0, dW[0], 7, nullptr, 0, part[0]),
-        plan_gemm(256, 256, B, g2, 1, 256, h[0], 256, 1, nullptr, 0, nullptr, 0, dW[1], 256, nullptr, 0, part[1]),
-        plan_gemm(256, 256, B, g3, 1, 256, h[1], 256, 1, nullptr, 0, nullptr, 0, dW[2], 256, nullptr, 0, part[2]),
-        plan_gemm(2, 256, B, g4, 1, 2, h[2], 256, 1, nullptr, 0, nullptr, 0, dW[3], 256, nullptr, 0, part[3])};
-    GemmGroup gg;
-    int splits[4];
-    gg.first[0] = 0;
-    for (int l = 0; l < 4; ++l) {
-        gg.g[l] = pw[l].g;
-        gg.tx[l] = pw[l].tx;
-        gg.ty[l] = pw[l].ty;
-        gg.first[l + 1] = gg.first[l] + pw[l].tx * pw[l].ty * pw[l].splits;
-        splits[l] = pw[l].splits;
+    auto take = [&](size_t elements) { uint16_t* q = (uint16_t*)p; p += al(2 * elements); return q; };
+    const size_t R = rows32(B);
+    TrainIO io;
+    UpdateArgs u;
+    io.w3 = net->wb[3];
+    io.feat = feat; io.label = label; io.target = target; io.idx = idx;
+    io.n = B;
+    io.out = (float*)(w0 + off[4]);
+    io.loss = loss;
+    io.x_out = (uint16_t*)(w0 + off[0]);
+    io.gout = (uint16_t*)(w0 + off[5]);
+    io.xT = take(R * kFeatLd);
+    io.g4T = take(R * 2);
+    for (int l = 0; l < 3; ++l) {
+        io.h_out[l] = (uint16_t*)(w0 + off[1 + l]);
+        io.g_out[l] = (uint16_t*)(w0 + off[8 - l]);
+        io.hT[l] = take(R * 256);
+        io.gT[l] = take(R * 256);
+        u.g[l] = io.gT[l];
+        u.a[l + 1] = io.hT[l];
     }
-    BiasArgs& ba = gg.bias;
-    const uint16_t* gl[4] = {g1, g2, g3, g4};
-    ba.rows = B;
-    ba.first[0] = 0;
-    for (int l = 0; l < 4; ++l) {
-        ba.G[l] = gl[l];
-        ba.ldg[l] = kOut[l];
-        ba.db[l] = db[l];
-        ba.first[l + 1] = ba.first[l] + kOut[l];
+    u.g[3] = io.g4T;
+    u.a[0] = io.xT;
+    for (int t = 0; t < 2; ++t) {
+        io.wf[t] = u.wf[t] = take(256 * 256);
+        io.wt[t] = u.wt[t] = take(256 * 256);
     }
-    hipLaunchKernelGGL(k_gemm_group, dim3(gg.first[4] + ba.first[4]), dim3(256), 0, s, gg);
-    // Adam on the FP32 master weights, refreshing the bfloat16 copies.
-    AdamArgs a;
-    a.lr = lr;
-    a.c1 = 1.0f - powf(0.9f, (float)step);
-    a.c2 = 1.0f - powf(0.999f, (float)step);
-    a.off[0] = 0;
+    io.w0 = u.w0p = take(256 * 8);
+    u.blocks8 = (int)(R / 8);
     for (int l = 0; l < 4; ++l) {
-        const int tw = 2 * l, tb = 2 * l + 1;
-        a.w[tw] = net->w[l]; a.g[tw] = dW[l]; a.m[tw] = net->mw[l]; a.v[tw] = net->vw[l]; a.wb[tw] = net->wb[l];
-        a.wbT[tw] = (l == 1 || l == 2) ? wT[l - 1] : nullptr;
-        a.part[tw] = part[l]; a.splits[tw] = splits[l];
-        a.off[tw + 1] = a.off[tw] + (int64_t)kIn[l] * kOut[l];
-        a.w[tb] = net->b[l]; a.g[tb] = db[l]; a.m[tb] = net->mb[l]; a.v[tb] = net->vb[l]; a.wb[tb] = nullptr;
-        a.wbT[tb] = nullptr;
-        a.part[tb] = nullptr; a.splits[tb] = 1;
-        a.off[tb + 1] = a.off[tb] + kOut[l];
+        io.b[l] = net->b[l];
+        gradient_splits(l, B, u.chunk[l], u.splits[l]);
+        u.w[l] = net->w[l]; u.mw[l] = net->mw[l]; u.vw[l] = net->vw[l]; u.wb[l] = net->wb[l];
+        u.b[l] = net->b[l]; u.mb[l] = net->mb[l]; u.vb[l] = net->vb[l];
     }
-    hipLaunchKernelGGL(k_adam, dim3(blocks_for(a.off[8], 256)), dim3(256), 0, s, a);
+    u.lr = lr;
+    u.c1 = 1.0f - powf(0.9f, (float)step);
+    u.c2 = 1.0f - powf(0.999f, (float)step);
+    if (fresh)
+        hipLaunchKernelGGL(k_pack_weights, dim3(520), dim3(256), 0, stream, net->wb[0], net->wb[1], net->wb[2], u.w0p,
+                           u.wf[0], u.wf[1], u.wt[0], u.wt[1]);
+    hipLaunchKernelGGL(k_mlp_train, dim3(blocks_for(B, kTrainFT)), dim3(512), 0, stream, io);
+    hipLaunchKernelGGL(k_mlp_update, dim3(kUpBlocks), dim3(64 * kUpWaves), 0, stream, u);
     return launched("pn_mlp_train_step");
 }
 
