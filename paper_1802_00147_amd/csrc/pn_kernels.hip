@@ -298,8 +298,11 @@ __device__ __forceinline__ void pair_ends(PairState& ps, const FliArgs& fa, int6
 }
 
 // Separation of the pair, computed identically in both lanes: the lanes form
-// e and -e exactly, so e * e and the sum carry the same bits.
+// e and -e exactly, so e * e and the sum carry the same bits.  Contraction is
+// off: a difference fused with the product that formed y in one lane would not
+// be the other lane's with its sign turned.
 __device__ __forceinline__ double pair_d2(const double* y) {
+#pragma clang fp contract(off)
     double d2 = 0.0;
 #pragma unroll
     for (int c = 0; c < 12; ++c) {

@@ -56,3 +56,24 @@ def test_momentum_scaling_iterations(pn, off, max_iter):
     it = pn.manifold_correct(yg, dev(ref.T), dev(betas), dev(np.full(100, 0.8)), dev(np.full(100, 0.6)), correction=corr)
     assert np.all(rel_err_rows(from_soa(yg), exp) <= 1e-12)
     assert np.mean(it.cpu().numpy() == it_exp) >= 0.95
+
+
+@pytest.mark.parametrize("shared", [True, False])
+@pytest.mark.parametrize("method", ["rk4", "rk5"])
+@pytest.mark.parametrize("mode", ["none", "spin", "six", "dual"])
+def test_last_trace_row_is_the_fli(pn, shared, method, mode):
+    """The separation inside the step loop and the one after it are the same
+    function of the same states, with one value for both lanes of a pair: a
+    trace row at the last step equals the FLI bit for bit, on the plain,
+    balanced and batch kernels alike."""
+    n, steps = 65, 60
+    ys, betas = orbit_states(O, np.random.default_rng(213), n, beta=0.5 if shared else None)
+    par = (0.5, 0.8, 0.6) if shared else (dev(betas), dev(np.full(n, 0.8)), dev(np.full(n, 0.6)))
+    kw = dict(integrator=dict(method=method), correction=dict(mode=mode), trace_every=20)
+    y0 = to_soa(ys)
+    t_end = torch.full((n,), float(steps), dtype=torch.float64, device=y0.device)
+    for out in (pn.fli_scan(y0, float(steps), *par, **kw), pn.fli_scan_balanced(y0, float(steps), *par, slots=7, **kw),
+                pn.batch_scan(y0, t_end, *par, **kw)):
+        ok = (out["status"] & 0xFF) == 0
+        assert bool(ok.any())
+        assert torch.equal(out["trace"][-1][ok].view(torch.int64), out["fli"][ok].view(torch.int64))
