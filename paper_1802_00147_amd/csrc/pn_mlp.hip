@@ -21,6 +21,7 @@
 #include <cstdio>
 #include <cstring>
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "pn.h"
@@ -541,17 +542,26 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
 }
 
 // Inference as a two-stage pipeline over 32-row tiles, one barrier per
-// tile.  In step k wavefronts 0-3 (the front stage) run layer 2 of tile k
-// and then layer 1 of tile k + 1, while wavefronts 4-7 (the back stage) run
-// layer 3 of tile k - 1 and then layer 4 of tile k - 2.  Every activation
-// buffer is doubled (tile parity), so within a step no wavefront writes a
-// buffer another one reads, and a buffer written in step k is read in step
-// k + 1, after the barrier.  Each wavefront keeps the B fragments of ONE
-// hidden layer for 64 output columns (4 column blocks x 8 K-slices; the same
+// tile.  Wavefronts 0-3 (the front stage) run layer 2 of tile k in step k, and
+// layer 1 of tile k + 1; wavefronts 4-7 (the back stage) run layer 3 of tile k - 2
+// and layer 4 of tile k - 4.  Each wavefront keeps the B fragments of ONE hidden
+// layer for 64 output columns (4 column blocks x 8 K-slices; the same
 // registers hold W2 in the front stage and W3 in the back), so every A
 // fragment read from LDS feeds four MFMAs, and both wavefronts of a SIMD
 // issue a hidden layer's MFMAs in the same step.  The hidden layer's biases
 // sit in registers, layer 1's biases and the two output rows in LDS.
+//
+// The matrix cores set the pace only if no wavefront waits for LDS or for a
+// result with nothing else to issue.  So a hidden layer is 16 groups of four
+// MFMAs whose fragment was requested three groups before, the conversions and
+// stores of the other blocks stand between them, and the last row block's
+// epilogue is left for after the next barrier, where it covers the first
+// fragments' way.  That costs a third buffer of h2 and h3 (tile modulo 3: the
+// first half written in one step, the second in the next, read in the third)
+// and two more steps at the end.  4,194,304 rows: 859 us with two buffers and
+// unordered groups (58% of the cycles with an MFMA in flight), 799 now (68%).
+// The clock falls from 2.31 to 2.11 GHz as the cores fill, so fewer cycles
+// shorten the time by less: from here power bounds the kernel.
 // Products, K-slice order, bias-started accumulators and the bfloat16 ReLU
 // epilogue are those of k_gemm_bf16: the outputs equal the
 // layer-by-layer path bit for bit.
@@ -564,11 +574,11 @@ __global__ __launch_bounds__(512) void k_mlp_infer(const uint16_t* __restrict__ 
                                                   const float* __restrict__ feat, int64_t n, float* __restrict__ out) {
     constexpr int FT = kInferFT, RB = FT / 16;
     __shared__ __attribute__((aligned(16))) uint16_t h1[2][FT][FLD];
-    __shared__ __attribute__((aligned(16))) uint16_t h2[2][FT][FLD];
-    __shared__ __attribute__((aligned(16))) uint16_t h3[2][FT][FLD];
+    __shared__ __attribute__((aligned(16))) uint16_t h2[3][FT][FLD];
+    __shared__ __attribute__((aligned(16))) uint16_t h3[3][FT][FLD];
     __shared__ __attribute__((aligned(16))) float bs[1][256];      // layer 1's biases
     __shared__ __attribute__((aligned(16))) uint16_t w4s[2][256];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int lr = lane & 15, lq = lane >> 4, lk = lq * 8;
     const bool front = wave < 4;                      // uniform per wavefront
     const int c0 = 64 * (wave & 3);                   // first output column of this wavefront's layer
@@ -617,97 +627,176 @@ __global__ __launch_bounds__(512) void k_mlp_infer(const uint16_t* __restrict__ 
             fnext[i][1] = *reinterpret_cast<const float4*>(feat + row * kFeatLd + 4);
         }
     };
-    // Epilogue of this wavefront's 64 columns (weights as the first MFMA
-    // operand: element v of lane l is tile row l % 16, column 4 (l / 16) + v
-    // of the 16-column block).
-    auto store = [&](uint16_t (*h)[FLD], f32x4 (&acc)[RB][4]) {
-#pragma unroll
-        for (int i = 0; i < RB; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint2 u;
-                u.x = relu_bf16x2(pack_bf16x2(acc[i][j][0], acc[i][j][1]));
-                u.y = relu_bf16x2(pack_bf16x2(acc[i][j][2], acc[i][j][3]));
-                *reinterpret_cast<uint2*>(&h[16 * i + lr][c0 + 16 * j + 4 * lq]) = u;
-            }
+    // Epilogue of column block j of a 16-row block (weights as the first MFMA
+    // operand: element v of lane l is tile row l % 16, column 4 (l / 16) + v of the
+    // 16-column block).
+    auto store = [&](uint16_t (*h)[FLD], int i, int j, const f32x4& x) {
+        uint2 u;
+        u.x = relu_bf16x2(pack_bf16x2(x[0], x[1]));
+        u.y = relu_bf16x2(pack_bf16x2(x[2], x[3]));
+        *reinterpret_cast<uint2*>(&h[16 * i + lr][c0 + 16 * j + 4 * lq]) = u;
     };
-    // Layer 1 of the tile whose features are in fnext, into h.
-    auto layer1 = [&](uint16_t (*h)[FLD]) {
-        f32x4 acc[RB][4];
-        f32x4 b0v[4];
+    // Row block i of the tile whose features are in fnext, as a fragment.
+    auto feat_frag = [&](int i) {
+        uint16_t v[8];
+        v[0] = f2bf(fnext[i][0].x); v[1] = f2bf(fnext[i][0].y); v[2] = f2bf(fnext[i][0].z);
+        v[3] = f2bf(fnext[i][0].w); v[4] = f2bf(fnext[i][1].x); v[5] = f2bf(fnext[i][1].y);
+        v[6] = f2bf(fnext[i][1].z); v[7] = 0;
+        return *reinterpret_cast<const bf16x8*>(v);
+    };
+    auto bias1 = [&](int j) { return *reinterpret_cast<const f32x4*>(&bs[0][c0 + 16 * j + 4 * lq]); };
+    // A hidden layer of one tile (W2 in the front stage, W3 in the back) as 16
+    // groups of one K slice of one row block: group m = 8 i + s takes its fragment
+    // from the ring, requests that of group m + 3 and issues four MFMAs, and side(m)
+    // adds the other work that belongs there.  Nothing moves between groups.
+    f32x4 x[2][4];
+    bf16x8 ring[4];
+    auto request = [&](uint16_t (*hin)[FLD], int m) {
+        ring[m & 3] = load_bf16x8(&hin[16 * (m >> 3) + lr][32 * (m & 7) + lk]);
+    };
+    auto hidden = [&](uint16_t (*hin)[FLD], auto&& side) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) b0v[j] = *reinterpret_cast<const f32x4*>(&bs[0][c0 + 16 * j + 4 * lq]);
-#pragma unroll
-        for (int i = 0; i < RB; ++i) {
-            uint16_t v[8];
-            v[0] = f2bf(fnext[i][0].x); v[1] = f2bf(fnext[i][0].y); v[2] = f2bf(fnext[i][0].z);
-            v[3] = f2bf(fnext[i][0].w); v[4] = f2bf(fnext[i][1].x); v[5] = f2bf(fnext[i][1].y);
-            v[6] = f2bf(fnext[i][1].z); v[7] = 0;
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(v);
+        for (int m = 0; m < 16; ++m) {
+            if (m + 3 < 16) request(hin, m + 3);
+            const int i = m >> 3, sl = m & 7;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf0[j], a, b0v[j], 0, 0, 0);
+                x[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j][sl], ring[m & 3], sl == 0 ? bh[j] : x[i][j], 0,
+                                                                  0, 0);
+            side(m);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        store(h, acc);
     };
-    // A hidden layer (1: W2, front; 2: W3, back), accumulators started at the bias.
-    auto hidden = [&](uint16_t (*hin)[FLD], uint16_t (*hout)[FLD]) {
-        f32x4 acc[RB][4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int i = 0; i < RB; ++i) acc[i][j] = bh[j];
-#pragma unroll
-        for (int sl = 0; sl < 8; ++sl)
-#pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                const bf16x8 a = load_bf16x8(&hin[16 * i + lr][32 * sl + lk]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j][sl], a, acc[i][j], 0, 0, 0);
-            }
-        store(hout, acc);
+    auto begin = [&](uint16_t (*hin)[FLD]) {
+        request(hin, 0);
+        request(hin, 1);
+        request(hin, 2);
     };
     __syncthreads();                                  // layer 1's biases and output rows in LDS
-    if (front && mine > 0) {
-        load_feat(tile_of(0));
-        layer1(h1[0]);
-        if (mine > 1) load_feat(tile_of(1));
-    }
-    __syncthreads();
-    for (int64_t k = 0; k <= mine + 1; ++k) {
-        const int p = (int)(k & 1);
-        if (front) {
-            if (k < mine) hidden(h1[p], h2[p]);
-            if (k + 1 < mine) {
-                layer1(h1[p ^ 1]);
-                if (k + 2 < mine) load_feat(tile_of(k + 2));
-            }
-        } else {
-            if (k >= 1 && k <= mine) hidden(h2[p ^ 1], h3[p ^ 1]);
-            // Layer 4, row block wave - 4 of tile k - 2 (parity p): outputs 0
-            // and 1 in columns 0 and 1; the other lanes' B operands (copies of
-            // row lane % 2) feed columns that are never stored.
-            if (k >= 2 && wave - 4 < RB) {
-                const int i = wave - 4;
-                const int64_t r0 = tile_of(k - 2) * FT;
-                f32x4 o = f32x4{bias3, bias3, bias3, bias3};
+    if (front) {
+        f32x4 y[4];
+        auto layer1 = [&](int i) {
+            const bf16x8 a = feat_frag(i);
 #pragma unroll
-                for (int sl = 0; sl < 8; ++sl) {
-                    const bf16x8 a = load_bf16x8(&h3[p][16 * i + lr][32 * sl + lk]);
-                    const bf16x8 b = load_bf16x8(&w4s[lr & 1][32 * sl + lk]);
-                    o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, o, 0, 0, 0);
-                }
+            for (int j = 0; j < 4; ++j) y[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf0[j], a, y[j], 0, 0, 0);
+        };
+        auto bias_y = [&]() {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) y[j] = bias1(j);
+        };
+        load_feat(tile_of(0));
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            bias_y();
+            layer1(i);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) store(h1[0], i, j, y[j]);
+        }
+        load_feat(tile_of(1));
+        bias_y();
+        int w = 0;                                    // h2 buffer of the tile
+        // Tile k: layer 2 (its second row block is stored after the next barrier),
+        // and layer 1 of tile k + 1.
+        auto tile = [&](auto later, int64_t k, uint16_t (*hin)[FLD], uint16_t (*h1n)[FLD], uint16_t (*hout)[FLD],
+                        uint16_t (*hprev)[FLD]) {
+            constexpr bool LATER = decltype(later)::value;      // a tile went before this one
+            begin(hin);
+            layer1(0);
+            __builtin_amdgcn_sched_barrier(0);
+            hidden(hin, [&](int m) {
+                if (LATER && m < 4) store(hprev, 1, m, x[1][m]);
+                if (m >= 2 && m < 6) store(h1n, 0, m - 2, y[m - 2]);
+                if (m == 6) bias_y();
+                if (m == 8) layer1(1);
+                if (m == 9) load_feat(tile_of(k + 2));
+                if (m >= 10 && m < 14) store(hout, 0, m - 10, x[0][m - 10]);
+                if (m >= 12) store(h1n, 1, m - 12, y[m - 12]);
+                if (m == 15) bias_y();
+            });
+        };
+        __syncthreads();
+        tile(std::false_type{}, 0, h1[0], h1[1], h2[0], h2[0]);
+        for (int64_t k = 1; k < mine; ++k) {
+            const int v = w;
+            w = w == 2 ? 0 : w + 1;
+            __syncthreads();
+            tile(std::true_type{}, k, h1[k & 1], h1[1 - (k & 1)], h2[w], h2[v]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) store(h2[w], 1, j, x[1][j]);
+        __syncthreads();
+        __syncthreads();
+        __syncthreads();
+    } else {
+        // Layer 4, row block wave - 4: outputs 0 and 1 in columns 0 and 1; the other
+        // lanes' B operands (copies of row lane % 2) feed columns that are never
+        // stored.
+        auto back = [&](auto last) {
+            constexpr bool LAST = decltype(last)::value;       // this wavefront runs layer 4
+            const int i4 = LAST ? wave - 4 : 0;
+            f32x4 o;
+            // The operands of slice s are requested two groups before their MFMA.
+            bf16x8 a4[2], w4[2];
+            auto request4 = [&](uint16_t (*h)[FLD], int sl) {
+                a4[sl & 1] = load_bf16x8(&h[16 * i4 + lr][32 * sl + lk]);
+                w4[sl & 1] = load_bf16x8(&w4s[lr & 1][32 * sl + lk]);
+            };
+            auto layer4 = [&](int sl) {
+                o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    a4[sl & 1], w4[sl & 1], sl == 0 ? f32x4{bias3, bias3, bias3, bias3} : o, 0, 0, 0);
+            };
+            auto output = [&](int64_t t) {
                 if (lr < 2) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const int64_t row = r0 + 16 * i + 4 * lq + v;
+                        const int64_t row = t * FT + 16 * i4 + 4 * lq + v;
                         if (row < n) out[row * 2 + lr] = o[v];
                     }
                 }
+            };
+            auto tile = [&](auto later, uint16_t (*hin)[FLD], uint16_t (*hout)[FLD], uint16_t (*hprev)[FLD],
+                            uint16_t (*h4)[FLD]) {
+                constexpr bool LATER = decltype(later)::value;
+                begin(hin);
+                hidden(hin, [&](int m) {
+                    if (LATER && m < 4) store(hprev, 1, m, x[1][m]);
+                    if (LATER && LAST) {              // slice s: requested in group s, used in s + 2
+                        if (m >= 2 && m < 10) layer4(m - 2);
+                        if (m < 8) request4(h4, m);
+                    }
+                    if (m >= 10 && m < 14) store(hout, 0, m - 10, x[0][m - 10]);
+                });
+            };
+            int w = 0;                                // h2 and h3 buffer of the tile
+            __syncthreads();
+            __syncthreads();
+            __syncthreads();
+            tile(std::false_type{}, h2[0], h3[0], h3[0], h3[0]);
+            for (int64_t t = 1; t < mine; ++t) {
+                const int v = w, l4 = w == 0 ? 2 : w - 1;      // tiles t - 1 and t - 2
+                w = w == 2 ? 0 : w + 1;
+                __syncthreads();
+                tile(std::true_type{}, h2[w], h3[w], h3[v], h3[l4]);
+                if (LAST && t >= 2) output(tile_of(t - 2));
             }
-        }
-        __syncthreads();
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < 4; ++j) store(h3[w], 1, j, x[1][j]);
+            if (LAST && mine >= 2) {
+#pragma unroll
+                for (int sl = 0; sl < 8; ++sl) { request4(h3[w == 0 ? 2 : w - 1], sl); layer4(sl); }
+                output(tile_of(mine - 2));
+            }
+            __syncthreads();
+            if (LAST) {
+#pragma unroll
+                for (int sl = 0; sl < 8; ++sl) { request4(h3[w], sl); layer4(sl); }
+                output(tile_of(mine - 1));
+            }
+        };
+        if (wave - 4 < RB) back(std::true_type{});
+        else back(std::false_type{});
     }
 }
 
