@@ -371,7 +371,7 @@ __device__ __forceinline__ void pair_step(PairState& ps, const PnCoef& k, bool s
     const double r2 = dot3(ps.y[0], ps.y[1], ps.y[2], ps.y[0], ps.y[1], ps.y[2]);
     ps.d2 = pair_d2(ps.y);
     const bool fine = r2 >= fa.rmerge2 && r2 <= fa.resc2 && isfinite(ps.d2);
-    if (__ballot(!fine) != 0ull) {
+    if (__builtin_expect(__ballot(!fine) != 0ull, 0)) {
         // Orbit verdict first, then the shadow's (same order in both lanes).
         const int mine = pn_validity(ps.y, fa.rmerge2, fa.resc2);
         const int other = swap_pair_i32(mine);
@@ -379,7 +379,7 @@ __device__ __forceinline__ void pair_step(PairState& ps, const PnCoef& k, bool s
         ps.st = vo != PN_ORBIT_OK ? vo : vs;
         if (ps.st != PN_ORBIT_OK) return;
     }
-    if (ps.d2 >= fa.d_renorm2) {
+    if (__builtin_expect(ps.d2 >= fa.d_renorm2, 0)) {
         const double d = sqrt(ps.d2);
         ps.acc += log10(d / fa.d0);
         double yp[12];
@@ -397,7 +397,7 @@ __device__ __forceinline__ void pair_step(PairState& ps, const PnCoef& k, bool s
         ps.d2 = pair_d2(ps.y);
     }
     const int64_t tev = fa.out.trace_every;
-    if (tev > 0 && (ps.t % tev) == 0 && !shadow) {
+    if (__builtin_expect(tev > 0, 0) && (ps.t % tev) == 0 && !shadow) {
         const int64_t row = ps.t / tev - 1;
         if (row < fa.out.ntrace) fa.out.trace[row * fa.ld + i] = ps.acc + log10(sqrt(ps.d2) / fa.d0);
     }
