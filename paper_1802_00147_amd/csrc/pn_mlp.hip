@@ -308,17 +308,19 @@ constexpr int kTrainFT = 16;        // rows of a training tile
 // accumulators and epilogues are those of k_gemm_bf16.
 //
 // A tile is a chain of seven small products, so the time is latency: of the
-// weights (512 KB a workgroup, at 64 B a clock about 4 us), of the gathered rows
+// weights (512 KB a workgroup, 64 B a clock: 8,200 cycles), of the gathered rows
 // and of each stage.  Therefore
 //  - fragments come in fragment order, W2 and W3 before the tile starts, and
-//    W3^T and W2^T into the same registers as soon as the forward product of
-//    that matrix is through, behind the remaining forward stages;
+//    W3^T and W2^T into the same registers once the forward product of that matrix
+//    is through, a quarter at a time: a wavefront that asks for a whole operand at
+//    once stands 2,000 cycles until its last load is taken;
 //  - every wavefront forms the output layer and the loss gradient of all 16 rows
 //    itself, one row per lane with both outputs (weights as the first operand),
-//    so that the gradient is in place for g3's product without an exchange;
+//    so that the gradient is in place for g3's product without an exchange, and
+//    the loss's value comes after everything that another wavefront waits for;
 //  - ReLU masks stay in the lane that formed the activation.
 // 25 us at 2,048 rows before (weights row-major, loss on one wavefront with
-// a barrier on each side), 13.9 now.
+// a barrier on each side), 13 now.
 __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
     constexpr int FT = kTrainFT;
     __shared__ __attribute__((aligned(16))) uint16_t h1s[FT][FLD];
@@ -337,11 +339,13 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
     const uint16_t w4v = io.w3[tid];                  // 512 threads, 2 x 256 weights
 
     bf16x8 wf[2][2][8];                               // two 256-deep operands of this wavefront's columns
-    auto load_weights = [&](int slot, const uint16_t* F) {
+    auto load_weights = [&](int slot, const uint16_t* F, int s0, int s1) {   // K slices [s0, s1)
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int sl = s0; sl < s1; ++sl)
 #pragma unroll
-            for (int sl = 0; sl < 8; ++sl) wf[slot][j][sl] = load_frag(F, 2 * wave + j, sl, lane);
+            for (int j = 0; j < 2; ++j) wf[slot][j][sl] = load_frag(F, 2 * wave + j, sl, lane);
+        __builtin_amdgcn_sched_barrier(0);
     };
     // Layer 1 fragments (K = 7; only the lanes of K-group 0 carry values).
     bf16x8 wf0[2];
@@ -359,16 +363,12 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
     const float b40 = io.b[3][0], b41 = io.b[3][1];
     // The row's index and W2 are on their way; then the features, label and
     // target of row lr (the lanes of K-groups 1-3 meet zero weights), W3 behind them.
-    __builtin_amdgcn_sched_barrier(0);
-    load_weights(0, io.wf[0]);
-    __builtin_amdgcn_sched_barrier(0);
+    load_weights(0, io.wf[0], 0, 8);
     const float* fr = io.feat + (int64_t)src * kFeatLd;
     const float4 f0 = *reinterpret_cast<const float4*>(fr);
     const float4 f1 = *reinterpret_cast<const float4*>(fr + 4);
     const float lab = io.label[src], tgt = io.target[src];
-    __builtin_amdgcn_sched_barrier(0);
-    load_weights(1, io.wf[1]);
-    __builtin_amdgcn_sched_barrier(0);
+    load_weights(1, io.wf[1], 0, 8);
     w4s[tid >> 8][tid & 255] = w4v;               // read after barriers
 
     // Rows 4 lq .. of this tile below n, of the four this lane's elements
@@ -456,22 +456,20 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
     }
     activate(0, h1s);
     __syncthreads();
-    // Layer 2, then its operand's registers take W3^T.
+    // Layer 2; its operand's registers then take W3^T, in quarters.
     start(1);
     product(0, h1s);
-    __builtin_amdgcn_sched_barrier(0);
-    load_weights(0, io.wt[1]);
-    __builtin_amdgcn_sched_barrier(0);
+    load_weights(0, io.wt[1], 0, 2);
     activate(1, h2s);
     __syncthreads();
-    // Layer 3, then W2^T.
+    // Layer 3.
+    load_weights(0, io.wt[1], 2, 4);
     start(2);
     product(1, h2s);
-    __builtin_amdgcn_sched_barrier(0);
-    load_weights(1, io.wt[0]);
-    __builtin_amdgcn_sched_barrier(0);
+    load_weights(0, io.wt[1], 4, 6);
     activate(2, h3s);
     __syncthreads();
+    load_weights(0, io.wt[1], 6, 8);
     // Layer 4, weights first: lane l (K-group 0) gets both outputs of row l
     // in elements 0 and 1.  The first operand's rows above 1 are copies that
     // feed elements nobody reads.
@@ -482,35 +480,14 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
         const bf16x8 b = load_bf16x8(&h3s[lr][32 * sl + lk]);
         o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, o, 0, 0, 0);
     }
-    // Loss of the batch: binary cross-entropy of the logit plus Huber
-    // (delta 1) of the FLI output, averaged over the n rows, and its
-    // gradient.
+    load_weights(1, io.wt[0], 0, 2);
+    // Gradient of the loss: binary cross-entropy of the logit plus Huber
+    // (delta 1) of the FLI output, averaged over the n rows.
     uint16_t g40 = 0, g41 = 0;
-    {
-        const float z = o[0], f = o[1], y = lab, d = f - tgt;
-        if (lq == 0 && live) {
-            const float sig = 1.0f / (1.0f + expf(-z));
-            g40 = f2bf((sig - y) / (float)n);
-            g41 = f2bf(fminf(fmaxf(d, -1.0f), 1.0f) / (float)n);
-        }
-        if (wave == 0) {
-            float l = 0.0f;
-            if (lq == 0) {
-                if (live) {
-                    l = fmaxf(z, 0.0f) - y * z + log1pf(expf(-fabsf(z)));
-                    l += fabsf(d) <= 1.0f ? 0.5f * d * d : fabsf(d) - 0.5f;
-                    *reinterpret_cast<float2*>(io.out + 2 * (r0 + lr)) = make_float2(z, f);
-                    *reinterpret_cast<uint32_t*>(io.gout + 2 * (r0 + lr)) = (uint32_t)g40 | ((uint32_t)g41 << 16);
-                }
-                uint16_t* T = io.g4T + (r0 / 8 + (lr >> 3)) * 2 * 8 + (lr & 7);
-                T[0] = g40;
-                T[8] = g41;
-                if (pad) T[2 * 2 * 8] = T[2 * 2 * 8 + 8] = 0;
-            }
-#pragma unroll
-            for (int off = 8; off > 0; off >>= 1) l += __shfl_xor(l, off);
-            if (lane == 0) atomicAdd(io.loss, l / (float)n);
-        }
+    if (lq == 0 && live) {
+        const float sig = 1.0f / (1.0f + expf(-o[0]));
+        g40 = f2bf((sig - lab) / (float)n);
+        g41 = f2bf(fminf(fmaxf(o[1] - tgt, -1.0f), 1.0f) / (float)n);
     }
     // g3 = (g4 W4) * (h3 > 0): K = 2, padded to one 32-deep slice.
     uint16_t y[2][4];
@@ -525,12 +502,15 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
             acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, *reinterpret_cast<const bf16x8*>(w), acc[j], 0, 0, 0);
         }
     }
+    load_weights(1, io.wt[0], 2, 4);
     masked(2, y);
     put(g3s, y, io.g_out[2], io.gT[2]);
     __syncthreads();
     // g2 = (g3 W3) * (h2 > 0).
+    load_weights(1, io.wt[0], 4, 6);
     start(-1);
     product(0, g3s);
+    load_weights(1, io.wt[0], 6, 8);
     masked(1, y);
     put(h3s, y, io.g_out[1], io.gT[1]);
     __syncthreads();
@@ -539,6 +519,27 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
     product(1, h3s);
     masked(0, y);
     put(h2s, y, io.g_out[0], io.gT[0]);
+    // The outputs, their gradient and the loss itself, behind everything that
+    // another wavefront waits for.
+    if (wave == 0) {
+        float l = 0.0f;
+        if (lq == 0) {
+            if (live) {
+                const float z = o[0], f = o[1], d = f - tgt;
+                l = fmaxf(z, 0.0f) - lab * z + log1pf(expf(-fabsf(z)));
+                l += fabsf(d) <= 1.0f ? 0.5f * d * d : fabsf(d) - 0.5f;
+                *reinterpret_cast<float2*>(io.out + 2 * (r0 + lr)) = make_float2(z, f);
+                *reinterpret_cast<uint32_t*>(io.gout + 2 * (r0 + lr)) = (uint32_t)g40 | ((uint32_t)g41 << 16);
+            }
+            uint16_t* T = io.g4T + (r0 / 8 + (lr >> 3)) * 2 * 8 + (lr & 7);
+            T[0] = g40;
+            T[8] = g41;
+            if (pad) T[2 * 2 * 8] = T[2 * 2 * 8 + 8] = 0;
+        }
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) l += __shfl_xor(l, off);
+        if (lane == 0) atomicAdd(io.loss, l / (float)n);
+    }
 }
 
 // Inference as a two-stage pipeline over 32-row tiles, one barrier per
