@@ -272,7 +272,9 @@ __device__ __forceinline__ bf16x8 load_frag(const uint16_t* F, int cb, int sl, i
 // second time in row-block order, element (r, c) of C columns at
 // ((r / 8) C + c) 8 + r % 8, with zeros in the rows from n up to the next multiple
 // of 32: there the eight rows that a lane of the weight gradients' products
-// takes lie together.  Hidden weights come in fragment order: wf[0], wf[1] =
+// takes lie together.  Only that copy is read; the row-major one is what a step
+// leaves for its caller, and without KEEP (a step whose workspace the next one
+// overwrites) it is not written.  Hidden weights come in fragment order: wf[0], wf[1] =
 // W2, W3 (columns: outputs), wt[0], wt[1] = W2, W3 transposed (columns: inputs);
 // W1 comes with its rows padded to eight values.
 struct TrainIO {
@@ -321,6 +323,7 @@ constexpr int kTrainFT = 16;        // rows of a training tile
 //  - ReLU masks stay in the lane that formed the activation.
 // 25 us at 2,048 rows before (weights row-major, loss on one wavefront with
 // a barrier on each side), 13 now.
+template <bool KEEP>
 __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
     constexpr int FT = kTrainFT;
     __shared__ __attribute__((aligned(16))) uint16_t h1s[FT][FLD];
@@ -394,6 +397,7 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
             *reinterpret_cast<uint2*>(T + (uint32_t)(offT + 256 * j)) = u;
             if (pad) *reinterpret_cast<uint2*>(T + (uint32_t)(offT + 256 * j + 8192)) = make_uint2(0u, 0u);
         }
+        if (!KEEP) return;
         __builtin_amdgcn_wave_barrier();
         const int r = lane >> 2;
         const uint4 q = *reinterpret_cast<const uint4*>(&h[r][c0 + 8 * (lane & 3)]);
@@ -445,7 +449,7 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wf0[j], acc[j], 0, 0, 0);
         if (wave == 0 && lq == 0) {
-            if (live) *reinterpret_cast<bf16x8*>(io.x_out + (r0 + lr) * kFeatLd) = a;
+            if (live && KEEP) *reinterpret_cast<bf16x8*>(io.x_out + (r0 + lr) * kFeatLd) = a;
             uint16_t* T = io.xT + (r0 / 8 + (lr >> 3)) * kFeatLd * 8 + (lr & 7);
 #pragma unroll
             for (int t = 0; t < 8; ++t) T[8 * t] = live ? v[t] : (uint16_t)0;
@@ -528,8 +532,10 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
                 const float z = o[0], f = o[1], d = f - tgt;
                 l = fmaxf(z, 0.0f) - lab * z + log1pf(expf(-fabsf(z)));
                 l += fabsf(d) <= 1.0f ? 0.5f * d * d : fabsf(d) - 0.5f;
-                *reinterpret_cast<float2*>(io.out + 2 * (r0 + lr)) = make_float2(z, f);
-                *reinterpret_cast<uint32_t*>(io.gout + 2 * (r0 + lr)) = (uint32_t)g40 | ((uint32_t)g41 << 16);
+                if (KEEP) {
+                    *reinterpret_cast<float2*>(io.out + 2 * (r0 + lr)) = make_float2(z, f);
+                    *reinterpret_cast<uint32_t*>(io.gout + 2 * (r0 + lr)) = (uint32_t)g40 | ((uint32_t)g41 << 16);
+                }
             }
             uint16_t* T = io.g4T + (r0 / 8 + (lr >> 3)) * 2 * 8 + (lr & 7);
             T[0] = g40;
@@ -1277,12 +1283,13 @@ void gradient_splits(int l, int batch, int& chunk, int& splits) {
 // before its first step.
 pn_status train_step(pn_mlp* net, const float* feat, const float* label, const float* target, const int32_t* idx,
                      int32_t batch, int32_t step, float lr, float* loss, void* ws, size_t ws_bytes,
-                     hipStream_t stream, bool fresh) {
+                     hipStream_t stream, bool fresh, bool keep) {
     if (!net_ok(net, true) || !feat || !label || !target || !idx || !loss) return PN_EINVAL;
     if ((reinterpret_cast<uintptr_t>(feat) & 15u) != 0) return PN_EINVAL;
     if (batch <= 0 || step < 1 || !(lr > 0.0f) || !std::isfinite(lr)) return PN_EINVAL;
     if (!ws || ws_bytes < pn_mlp_train_workspace_size(batch)) return PN_ENOWS;
-    if (device_cu_count() <= 0) {
+    const int ncu = device_cu_count();
+    if (ncu <= 0) {
         pn_detail::set_last_error("pn_mlp_train_step", "no device");
         return PN_EDEVICE;
     }
@@ -1334,7 +1341,16 @@ pn_status train_step(pn_mlp* net, const float* feat, const float* label, const f
     if (fresh)
         hipLaunchKernelGGL(k_pack_weights, dim3(520), dim3(256), 0, stream, net->wb[0], net->wb[1], net->wb[2], u.w0p,
                            u.wf[0], u.wf[1], u.wt[0], u.wt[1]);
-    hipLaunchKernelGGL(k_mlp_train, dim3(blocks_for(B, kTrainFT)), dim3(512), 0, stream, io);
+    // The tensors go out row-major for the caller (keep), and also where the tiles
+    // come close to one per CU: there the loads of all workgroups meet, and the
+    // stores between them cost nothing (16 steps, with and without: batch 2,048
+    // 326 and 312 us, 3,072 385 and 375, 3,584 403 and 407, 4,096 421 and 424, 8,192 658
+    // and 645).
+    const int tiles = (int)blocks_for(B, kTrainFT);
+    if (keep || (4 * (int64_t)tiles > 3 * ncu && tiles <= ncu))
+        hipLaunchKernelGGL(k_mlp_train<true>, dim3(tiles), dim3(512), 0, stream, io);
+    else
+        hipLaunchKernelGGL(k_mlp_train<false>, dim3(tiles), dim3(512), 0, stream, io);
     hipLaunchKernelGGL(k_mlp_update, dim3(kUpBlocks), dim3(64 * kUpWaves), 0, stream, u);
     return launched("pn_mlp_train_step");
 }
@@ -1346,7 +1362,7 @@ extern "C" {
 pn_status pn_mlp_train_step(pn_mlp* net, const float* feat, const float* label, const float* target,
                             const int32_t* idx, int32_t batch, int32_t step, float lr, float* loss,
                             void* ws, size_t ws_bytes, hipStream_t stream) {
-    return train_step(net, feat, label, target, idx, batch, step, lr, loss, ws, ws_bytes, stream, true);
+    return train_step(net, feat, label, target, idx, batch, step, lr, loss, ws, ws_bytes, stream, true, true);
 }
 
 pn_status pn_mlp_train(pn_mlp* net, int32_t* adam_step, const float* feat, const float* label, const float* target,
@@ -1357,7 +1373,7 @@ pn_status pn_mlp_train(pn_mlp* net, int32_t* adam_step, const float* feat, const
     if ((int64_t)*adam_step + nbatch > 0x7fffffffLL) return PN_EINVAL;
     for (int64_t b = 0; b < nbatch; ++b) {
         const pn_status st = train_step(net, feat, label, target, order + b * batch, batch, *adam_step + 1, lr,
-                                        loss, ws, ws_bytes, stream, b == 0);
+                                        loss, ws, ws_bytes, stream, b == 0, b == nbatch - 1);
         if (st != PN_OK) return st;
         *adam_step += 1;
     }
@@ -1746,7 +1762,7 @@ pn_status pn_surrogate_scan(pn_mlp* net, int32_t* adam_step, const pn_model* mod
                     PN_TRY(train_step(net, featA, labA, tgtA, order + (size_t)k * nv + b * cfg->refine_batch,
                                       cfg->refine_batch, *adam_step, lr_e, loss, tws,
                                       pn_mlp_train_workspace_size(cfg->refine_batch), stream,
-                                      e == 0 && b == 0));
+                                      e == 0 && b == 0, false));
                 }
             }
             PN_HIP(hipStreamSynchronize(stream), what);    // the host buffer is refilled next

@@ -70,3 +70,18 @@ def test_weight_copies_follow_the_updates(pn, B):
         for x, y in ((one.w, many.w), (one.b, many.b), (one.vw, many.vw), (one.mb, many.mb)):
             assert torch.equal(x[l].view(torch.int32), y[l].view(torch.int32)), l
         assert torch.equal(one.wb[l].view(torch.bfloat16), one.w[l].to(torch.bfloat16)), l
+
+
+@pytest.mark.parametrize("B", [33, 2048, 3600])
+def test_last_step_leaves_its_tensors(pn, B):
+    """Three steps of one call leave the third step's tensors in the workspace,
+    as a single step from the same weights does: the same bits."""
+    one, feat, lab, tgt, idx = inputs(pn, 63, rows=12000)
+    many = inputs(pn, 63, rows=12000)[0]
+    loss = torch.zeros(1, device=DEV)
+    ws = pn.mlp_train(one, feat, lab, tgt, idx[:3 * B].contiguous(), B, 1e-3, loss)
+    for b in range(3):
+        ws1 = pn.mlp_train_step(many, feat, lab, tgt, idx[b * B:(b + 1) * B].contiguous(), 1e-3, loss)
+    a, c = pn.mlp_train_step_tensors(ws, B), pn.mlp_train_step_tensors(ws1, B)
+    for k in a:
+        assert torch.equal(a[k].view(torch.int32 if k == "out" else torch.int16), c[k].view(torch.int32 if k == "out" else torch.int16)), k
