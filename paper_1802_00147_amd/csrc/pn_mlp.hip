@@ -1229,8 +1229,13 @@ size_t pn_mlp_param_count(int32_t layer, int32_t which) {
 size_t pn_mlp_train_workspace_size(int32_t batch) {
     if (batch <= 0) return 0;
     const size_t B = (size_t)batch, R = rows32(batch);
+    const size_t own = al(R * kFeatLd * 2) + 6 * al(R * 256 * 2) + al(R * 2 * 2) + 4 * al(256 * 256 * 2) + al(256 * 8 * 2);
+    // The interface promises room for FP32 gradients, four 4 MB buffers and two
+    // transposed weights behind the reported tensors; up to about 5500 rows the
+    // step's own buffers are smaller than that.
+    const size_t promised = (2 * 256 * 256 + 256 * 7 + 2 * 256 + 4 * 256) * 4 + 4 * ((size_t)1 << 22) + 2 * 256 * 256 * 2;
     return al(B * kFeatLd * 2) + 3 * al(B * 256 * 2) + al(B * 2 * 4) + al(B * 2 * 2) + 3 * al(B * 256 * 2) +
-           al(R * kFeatLd * 2) + 6 * al(R * 256 * 2) + al(R * 2 * 2) + 4 * al(256 * 256 * 2) + al(256 * 8 * 2);
+           (own > promised ? own : promised);
 }
 
 pn_status pn_mlp_train_workspace_layout(int32_t batch, size_t* off) {
