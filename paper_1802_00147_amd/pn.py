@@ -145,6 +145,21 @@ def lib():
     return _lib
 
 
+_protos = {}
+
+
+def _proto(name, *argtypes):
+    """The entry point `name` with its argument types declared, so that plain
+    integers pass as pointers: a few points are predicted in less time than it
+    takes to wrap each argument in an object."""
+    f = _protos.get(name)
+    if f is None:
+        f = lib()[name]                 # a function object of its own, not the attribute's
+        f.restype, f.argtypes = ctypes.c_int, argtypes
+        _protos[name] = f
+    return f
+
+
 def _defaults(struct, fill):
     s = struct()
     getattr(lib(), fill)(ctypes.byref(s))
@@ -183,8 +198,20 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+# Handle of a device's current stream without a Stream object around it
+# (0.1 us instead of 2).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_handle(device):
+    if (_raw_stream is not None and isinstance(device, torch.device) and device.type == "cuda"
+            and device.index is not None and torch.cuda.is_initialized()):
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
+
+
 def _stream(device=None):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return ctypes.c_void_p(_stream_handle(device))
 
 
 def _check(fn, st):
@@ -230,7 +257,7 @@ def _dev_f64(t, n=None):
 def params_struct(beta, chi1, chi2):
     """Scalars give one shared parameter set; tensors give per-orbit device arrays.
     Returns (struct, keepalive)."""
-    if all(isinstance(v, torch.Tensor) for v in (beta, chi1, chi2)):
+    if isinstance(beta, torch.Tensor) and isinstance(chi1, torch.Tensor) and isinstance(chi2, torch.Tensor):
         keep = [_dev_f64(v) for v in (beta, chi1, chi2)]
         return Params(keep[0].data_ptr(), keep[1].data_ptr(), keep[2].data_ptr(), 0.0, 0.0, 0.0), keep
     return Params(None, None, None, float(beta), float(chi1), float(chi2)), []
@@ -705,20 +732,25 @@ class Network:
                 for W, b in zip(self.w, self.b)]
 
 
+_F7 = ctypes.c_float * 7
+
+
 def mlp_features(n, r0, th1, th2, t_end, beta, chi1, chi2, mean, std, idx=None, out=None):
     """Standardised features [n, 8] (FP32) of scan points."""
     dev_ = r0.device
     if out is None:
         out = torch.empty((n, 8), dtype=torch.float32, device=dev_)
     p, keep = params_struct(beta, chi1, chi2)
-    mean = (ctypes.c_float * 7)(*[float(x) for x in mean])
-    std = (ctypes.c_float * 7)(*[float(x) for x in std])
     if isinstance(t_end, torch.Tensor):
-        tptr, tall = _ptr(_dev_f64(t_end)), 0.0
+        t_end = _dev_f64(t_end)
+        tptr, tall = t_end.data_ptr(), 0.0
     else:
         tptr, tall = None, float(t_end)
-    st = lib().pn_mlp_features(p, ctypes.c_int64(n), _ptr(_dev_f64(r0)), _ptr(_dev_f64(th1)), _ptr(_dev_f64(th2)),
-                               tptr, ctypes.c_double(tall), _ptr(idx), mean, std, _ptr(out), _stream(dev_))
+    r0, th1, th2 = _dev_f64(r0), _dev_f64(th1), _dev_f64(th2)
+    v = ctypes.c_void_p
+    st = _proto("pn_mlp_features", Params, ctypes.c_int64, v, v, v, v, ctypes.c_double, v, v, v, v, v)(
+        p, n, r0.data_ptr(), th1.data_ptr(), th2.data_ptr(), tptr, tall, None if idx is None else idx.data_ptr(),
+        _F7(*map(float, mean)), _F7(*map(float, std)), out.data_ptr(), _stream_handle(dev_))
     _check("pn_mlp_features", st)
     return out
 
@@ -807,9 +839,11 @@ def mlp_infer_fused(net, feat, out=None):
     n = _feat_rows(feat)
     if out is None:
         out = torch.empty((n, 2), dtype=torch.float32, device=feat.device)
-    _dev(out, torch.float32, "out", shape=(n, 2))
-    st = lib().pn_mlp_infer_fused(ctypes.byref(net.struct), _ptr(feat), ctypes.c_int64(n), _ptr(out),
-                                  _stream(feat.device))
+    else:
+        _dev(out, torch.float32, "out", shape=(n, 2))
+    v = ctypes.c_void_p
+    st = _proto("pn_mlp_infer_fused", v, v, ctypes.c_int64, v, v)(
+        ctypes.byref(net.struct), feat.data_ptr(), n, out.data_ptr(), _stream_handle(feat.device))
     _check("pn_mlp_infer_fused", st)
     return out
 
