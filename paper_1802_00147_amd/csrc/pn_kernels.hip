@@ -30,6 +30,14 @@ namespace {
 
 constexpr int kBlock = 64;  // one wavefront per workgroup
 
+// Lanes of a wavefront that have to be at work for full speed.  Where a CU has
+// no more than 32 lanes in FP64 work, its vector instructions wait: one orbit
+// takes 640 to 885 us for 256 RK4 steps, depending on the XCD it lands on, 33 or
+// 64 equal ones always 640; with one or two lanes in every wavefront of a full
+// chip a step takes four times as long as with all of them.  Lanes without an
+// orbit of their own therefore mirror one until that many are at work.
+constexpr int kFullLanes = 34;
+
 void set_error(const char* what, hipError_t e) { pn_detail::set_last_error(what, hipGetErrorString(e)); }
 
 // Parameters of a kernel: either per-orbit device arrays, or one shared
@@ -162,8 +170,10 @@ template <int METHOD, int MODE, bool RR>
 __global__ __launch_bounds__(kBlock) void k_step(ParamArgs pa, CorrArgs ca, double h, int64_t n,
                                                 double* y, int64_t ld, double* ref,
                                                 int64_t nsteps, double* traj, int64_t every, double eta0) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
+    // Lanes past the end run the last orbit again and store nothing: see kFullLanes.
+    const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const bool own = g < n;
+    const int64_t i = own ? g : n - 1;
     PnCoef k;
     load_coef(pa, i, k);
     double z[RR ? 16 : 12];
@@ -192,11 +202,12 @@ __global__ __launch_bounds__(kBlock) void k_step(ParamArgs pa, CorrArgs ca, doub
         bool nc;
         pn_correct<MODE>(k, s, r, ca.tol, ca.max_iter, ca.sweeps, nc, geo);
         if (row != nullptr && --left == 0) {
-            store_state(row, ld, i, s);
+            if (own) store_state(row, ld, i, s);
             row += 12 * ld;
             left = every;
         }
     }
+    if (!own) return;
     store_state(y, ld, i, s);
     if (RR && ref) {
 #pragma unroll
@@ -407,6 +418,45 @@ __device__ __forceinline__ bool pair_running(const PairState& ps) {
     return ps.st == PN_ORBIT_OK && ps.t < ps.nsteps;
 }
 
+// Lanes without work (idle) that are to mirror a working pair (live: the
+// lanes at work, whole pairs) so that kFullLanes are in flight.
+__device__ __forceinline__ bool lane_mirrors(unsigned long long live, bool idle) {
+    const int want = kFullLanes - __popcll(live);
+    const unsigned long long m = __ballot(idle);
+    const int even = threadIdx.x & 62;
+    return idle && __popcll(m & ((1ull << even) - 1ull)) < want;
+}
+
+// Copies the first live pair's trajectory (parameters, state, position) into
+// the lanes with `take`.  What only pair_finish reads is left out: a mirror
+// ends with its source and reports nothing.
+template <bool SHARED>
+__device__ __forceinline__ void pair_mirror(PairState& ps, PnCoef& k, int64_t& i, unsigned long long live,
+                                            bool take) {
+    const int src = __ffsll((long long)live) - 1 + (threadIdx.x & 1);
+    auto copy = [&](auto& v) {
+        const auto x = __shfl(v, src);
+        if (take) v = x;
+    };
+    if (!SHARED) {
+        double* const c = &k.a1;
+#pragma unroll
+        for (int q = 0; q < (int)(sizeof(PnCoef) / sizeof(double)); ++q) copy(c[q]);
+    }
+#pragma unroll
+    for (int c = 0; c < 12; ++c) copy(ps.y[c]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) copy(ps.ref[c]);
+    double* const ge = &ps.geo.u;
+#pragma unroll
+    for (int q = 0; q < (int)(sizeof(PnRhsGeom) / sizeof(double)); ++q) copy(ge[q]);
+    copy(ps.acc);
+    copy(ps.t);
+    copy(ps.nsteps);
+    copy(ps.st);
+    copy(i);
+}
+
 // Steps the wavefront runs before its next look for ended orbits or pieces:
 // up to the first one that ends (left: steps this pair still has to run; a
 // pair without work gives a large value), at least kMinRun, at most cap.  A
@@ -466,11 +516,18 @@ __device__ __forceinline__ void pair_finish(PairState& ps, const PnCoef& k, bool
 // Fused scan: orbit i on lanes (2i, 2i+1) from t = 0 to t_end.  SHARED:
 // every orbit has the parameter set of pa.coef, whose table then stays in
 // scalar registers.
+// Pairs without an orbit, from the start or once theirs has ended, mirror one
+// of the wavefront's others (kFullLanes): one orbit, 2,000 steps, 6.45-6.8 ms ->
+// 5.92; 1,000 orbits, 300 steps, 0.98 -> 0.84 (their last wavefront holds 8);
+// 4,096 with ends at merger 13.75 -> 13.6; a full chip is unchanged.  The bound
+// of two wavefronts per SIMD keeps RK4 with spins and parameters per orbit at
+// the 256 registers that the loop itself needs (36 bytes of what only the ends
+// use go to scratch: 98,596 orbits 2.08 -> 1.96 ms).
 template <int METHOD, int MODE, bool SHARED>
-__global__ __launch_bounds__(kBlock) void k_fli_scan(ParamArgs pa, FliArgs fa) {
+__global__ __launch_bounds__(kBlock, METHOD == PN_RK4 && MODE == PN_CORR_SPIN && !SHARED ? 2 : 1) void k_fli_scan(ParamArgs pa, FliArgs fa) {
     const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const int64_t i = g >> 1;
-    if (i >= fa.n) return;                 // pairs are whole: both lanes leave together
+    bool own = (g >> 1) < fa.n;            // the pair still has an orbit to report
+    int64_t i = own ? g >> 1 : fa.n - 1;
     const bool shadow = (g & 1) != 0;
     PnCoef k;
     bool param_ok = true;
@@ -482,8 +539,22 @@ __global__ __launch_bounds__(kBlock) void k_fli_scan(ParamArgs pa, FliArgs fa) {
     }
     PairState ps;
     pair_begin(ps, k, param_ok, shadow, fa, i);
-    while (pair_running(ps)) pair_step<METHOD, MODE>(ps, k, shadow, fa, i);
-    pair_finish(ps, k, shadow, fa, i);
+    for (;;) {
+        // The pairs that run, in lockstep, until the first of them ends.
+        if (pair_running(ps)) {
+            const unsigned long long live = __ballot(true);
+            do pair_step<METHOD, MODE>(ps, k, shadow, fa, i);
+            while (__ballot(pair_running(ps)) == live);
+        }
+        if (own && !pair_running(ps)) {
+            pair_finish(ps, k, shadow, fa, i);
+            own = false;
+        }
+        const unsigned long long left = __ballot(own);
+        if (left == 0ull) break;
+        const unsigned long long run = __ballot(pair_running(ps));
+        if (__popcll(run) < kFullLanes) pair_mirror<SHARED>(ps, k, i, left, lane_mirrors(run, !pair_running(ps)));
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -721,12 +792,21 @@ __global__ __launch_bounds__(256, OCC) void k_batch_scan(ParamArgs pa, FliArgs f
         // A checkpointed launch counts whole chunks; the others stop at the
         // first orbit that ends.
         const int run = CKPT ? chunk : wave_run(cur < 0 ? (int64_t)chunk : pair_running(ps) ? ps.nsteps - ps.t : 0, chunk);
-        if (cur >= 0) {
-            for (int c = 0; c < run && pair_running(ps); ++c) pair_step<METHOD, MODE>(ps, k, shadow, fa, cur);
-            if (!pair_running(ps)) {
-                pair_finish(ps, k, shadow, fa, cur);
-                cur = -1;
-            }
+        // Empty slots stay empty once the queue is drained; the last orbits of
+        // the wavefront are then mirrored in them.
+        bool work = cur >= 0;
+        int64_t i = cur;
+        const unsigned long long live = __ballot(work);
+        if (__popcll(live) < kFullLanes) {
+            const bool take = lane_mirrors(live, !work);
+            pair_mirror<false>(ps, k, i, live, take);
+            work = work || take;
+        }
+        if (work)
+            for (int c = 0; c < run && pair_running(ps); ++c) pair_step<METHOD, MODE>(ps, k, shadow, fa, i);
+        if (cur >= 0 && !pair_running(ps)) {
+            pair_finish(ps, k, shadow, fa, cur);
+            cur = -1;
         }
         if (CKPT && ck.max_chunks > 0 && ++chunks >= ck.max_chunks) {
             // Interrupted: save the pairs still running into the other table.
@@ -901,11 +981,22 @@ __global__ __launch_bounds__(256, OCC) void k_wrap_scan(ParamArgs pa, FliArgs fa
             open = false;
         }
         // Steps left in this launch: up to b, less what lies past tend.
-        const int64_t stop = pend <= tend ? b : b - (pend - tend);
+        int64_t stop = pend <= tend ? b : b - (pend - tend);
         const int run = wave_run(!active ? (int64_t)wa.chunk : ps.st == PN_ORBIT_OK ? stop - ps.t : 0, wa.chunk);
-        if (active) {
+        // Slots that are done stay idle: the others are mirrored in them.
+        bool work = active;
+        const unsigned long long live = __ballot(active);
+        if (__popcll(live) < kFullLanes) {
+            const bool take = lane_mirrors(live, !active);
+            pair_mirror<SHARED>(ps, k, orbit, live, take);
+            const int64_t end = __shfl(stop, __ffsll((long long)live) - 1);
+            if (take) stop = end;
+            work = active || take;
+        }
+        if (work)
             for (int c = 0; c < run && ps.st == PN_ORBIT_OK && ps.t < stop; ++c)
                 pair_step<METHOD, MODE>(ps, k, shadow, fa, orbit);
+        if (active) {
             if (!(ps.st == PN_ORBIT_OK && ps.t < stop)) {
                 if (pend > tend) {
                     rec_save(wa.carry, s, ps, shadow, orbit);
