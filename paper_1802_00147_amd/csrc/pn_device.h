@@ -705,33 +705,41 @@ __device__ void pn_rk_step_rr(const PnCoef& k, double eta, double* z, double h) 
         pn_rhs_rr(k, eta, z, k1);
         for (int c = 0; c < D; ++c) t[c] = fma(0.5 * h, k1[c], z[c]);
         pn_rhs_rr(k, eta, t, k2);
-        for (int c = 0; c < D; ++c) t[c] = fma(0.5 * h, k2[c], z[c]);
-        pn_rhs_rr(k, eta, t, k3);
-        for (int c = 0; c < D; ++c) t[c] = fma(h, k3[c], z[c]);
-        pn_rhs_rr(k, eta, t, k4);
-        for (int c = 0; c < D; ++c) z[c] = fma(h / 6.0, k1[c] + 2.0 * k2[c] + 2.0 * k3[c] + k4[c], z[c]);
+        for (int c = 0; c < D; ++c) { t[c] = fma(0.5 * h, k2[c], z[c]); k1[c] = fma(2.0, k2[c], k1[c]); }
+        pn_rhs_rr(k, eta, t, k2);
+        for (int c = 0; c < D; ++c) { t[c] = fma(h, k2[c], z[c]); k1[c] = fma(2.0, k2[c], k1[c]); }
+        pn_rhs_rr(k, eta, t, k2);
+        for (int c = 0; c < D; ++c) z[c] = fma(h / 6.0, k1[c] + k2[c], z[c]);
         return;
     }
-    double k5[D], k6[D];
+    // Dormand-Prince.  From the third stage on the sums of the later ones stand
+    // for the stage derivatives (four vectors live at most, not five), formed
+    // term by term in the order of the tableau's rows.
     pn_rhs_rr(k, eta, z, k1);
-    for (int c = 0; c < D; ++c) t[c] = z[c] + h * (1.0 / 5.0) * k1[c];
+    for (int c = 0; c < D; ++c) t[c] = fma(h * (1.0 / 5.0), k1[c], z[c]);
     pn_rhs_rr(k, eta, t, k2);
-    for (int c = 0; c < D; ++c) t[c] = z[c] + h * ((3.0 / 40.0) * k1[c] + (9.0 / 40.0) * k2[c]);
+    for (int c = 0; c < D; ++c) t[c] = fma(h, fma(3.0 / 40.0, k1[c], (9.0 / 40.0) * k2[c]), z[c]);
     pn_rhs_rr(k, eta, t, k3);
-    for (int c = 0; c < D; ++c)
-        t[c] = z[c] + h * ((44.0 / 45.0) * k1[c] + (-56.0 / 15.0) * k2[c] + (32.0 / 9.0) * k3[c]);
+    double s5[D], s6[D], acc[D];
+    for (int c = 0; c < D; ++c) {
+        t[c] = fma(h, fma(32.0 / 9.0, k3[c], fma(44.0 / 45.0, k1[c], (-56.0 / 15.0) * k2[c])), z[c]);
+        s5[c] = fma(64448.0 / 6561.0, k3[c], fma(19372.0 / 6561.0, k1[c], (-25360.0 / 2187.0) * k2[c]));
+        s6[c] = fma(46732.0 / 5247.0, k3[c], fma(9017.0 / 3168.0, k1[c], (-355.0 / 33.0) * k2[c]));
+        acc[c] = fma(35.0 / 384.0, k1[c], (500.0 / 1113.0) * k3[c]);
+    }
     pn_rhs_rr(k, eta, t, k4);
-    for (int c = 0; c < D; ++c)
-        t[c] = z[c] + h * ((19372.0 / 6561.0) * k1[c] + (-25360.0 / 2187.0) * k2[c] + (64448.0 / 6561.0) * k3[c] +
-                           (-212.0 / 729.0) * k4[c]);
-    pn_rhs_rr(k, eta, t, k5);
-    for (int c = 0; c < D; ++c)
-        t[c] = z[c] + h * ((9017.0 / 3168.0) * k1[c] + (-355.0 / 33.0) * k2[c] + (46732.0 / 5247.0) * k3[c] +
-                           (49.0 / 176.0) * k4[c] + (-5103.0 / 18656.0) * k5[c]);
-    pn_rhs_rr(k, eta, t, k6);
-    for (int c = 0; c < D; ++c)
-        z[c] = z[c] + h * ((35.0 / 384.0) * k1[c] + (500.0 / 1113.0) * k3[c] + (125.0 / 192.0) * k4[c] +
-                           (-2187.0 / 6784.0) * k5[c] + (11.0 / 84.0) * k6[c]);
+    for (int c = 0; c < D; ++c) {
+        t[c] = fma(h, fma(-212.0 / 729.0, k4[c], s5[c]), z[c]);
+        s6[c] = fma(49.0 / 176.0, k4[c], s6[c]);
+        acc[c] = fma(125.0 / 192.0, k4[c], acc[c]);
+    }
+    pn_rhs_rr(k, eta, t, k4);       // k5
+    for (int c = 0; c < D; ++c) {
+        t[c] = fma(h, fma(-5103.0 / 18656.0, k4[c], s6[c]), z[c]);
+        acc[c] = fma(-2187.0 / 6784.0, k4[c], acc[c]);
+    }
+    pn_rhs_rr(k, eta, t, k4);       // k6
+    for (int c = 0; c < D; ++c) z[c] = fma(h, fma(11.0 / 84.0, k4[c], acc[c]), z[c]);
 }
 
 // Orbit validity in the order: non-finite, merged, escaped.  The sum of

@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "pn.h"
 #include "pn_device.h"
@@ -166,7 +167,12 @@ __global__ __launch_bounds__(kBlock) void k_correct(ParamArgs pa, CorrArgs ca, i
 // RR: the dissipative system (2.5PN reaction); the references advance with
 // the state (z = (y, E, J), one RK step for all 16 components) and are
 // written back to ref when it is given.
-template <int METHOD, int MODE, bool RR>
+// SHARED: as in k_fli_scan.  The loop is bound by the instructions a lone
+// wavefront issues; with the table in scalar registers and the stage sums
+// folded as they form, the 256 vector registers hold nearly all of it: one
+// dissipative orbit, RK5, both corrections, 256 steps: 972 -> 904 us (226 of the
+// step's 2,030 instructions were register moves).
+template <int METHOD, int MODE, bool RR, bool SHARED>
 __global__ __launch_bounds__(kBlock) void k_step(ParamArgs pa, CorrArgs ca, double h, int64_t n,
                                                 double* y, int64_t ld, double* ref,
                                                 int64_t nsteps, double* traj, int64_t every, double eta0) {
@@ -175,7 +181,12 @@ __global__ __launch_bounds__(kBlock) void k_step(ParamArgs pa, CorrArgs ca, doub
     const bool own = g < n;
     const int64_t i = own ? g : n - 1;
     PnCoef k;
-    load_coef(pa, i, k);
+    if (SHARED) {
+        k = pa.coef;
+        pn_coef_derive(k);
+    } else {
+        load_coef(pa, i, k);
+    }
     double z[RR ? 16 : 12];
     double* const s = z;
     double rloc[4];
@@ -1101,12 +1112,16 @@ pn_status launched(const char* what) {
 template <int METHOD, int MODE>
 void launch_step(const ParamArgs& pa, const CorrArgs& ca, double h, int64_t n, double* y, int64_t ld,
                  double* ref, int64_t nsteps, double* traj, int64_t every, double eta0, hipStream_t s) {
+    auto launch = [&](auto rr, auto shared) {
+        hipLaunchKernelGGL((k_step<METHOD, MODE, decltype(rr)::value, decltype(shared)::value>), dim3(grid_for(n)),
+                           dim3(kBlock), 0, s, pa, ca, h, n, y, ld, ref, nsteps, traj, every, eta0);
+    };
+    const bool shared = pa.beta == nullptr;
     if (pa.model.rad_reaction)
-        hipLaunchKernelGGL((k_step<METHOD, MODE, true>), dim3(grid_for(n)), dim3(kBlock), 0, s, pa, ca, h, n, y,
-                           ld, ref, nsteps, traj, every, eta0);
-    else
-        hipLaunchKernelGGL((k_step<METHOD, MODE, false>), dim3(grid_for(n)), dim3(kBlock), 0, s, pa, ca, h, n, y,
-                           ld, ref, nsteps, traj, every, eta0);
+        shared ? launch(std::true_type{}, std::true_type{}) : launch(std::true_type{}, std::false_type{});
+    else        // RK4's step fits the registers with the table
+        shared ? launch(std::false_type{}, std::bool_constant<METHOD == PN_RK5>{})
+               : launch(std::false_type{}, std::false_type{});
 }
 
 template <int METHOD>
