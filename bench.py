@@ -46,7 +46,7 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6     # MI355X: 256 CU x 128 FP64 flop/clk x 2.4 GH
 # the RK4 step + 0.6k for the correction) + 40 for the separation.  The
 # oracle's counting scalar gives 7.7k: it evaluates H and its gradient
 # separately, and H again with dH/dp in every momentum-scaling iteration.
-# The kernel executes about 5.0k (FP64 instruction counters, FMA = 2).  The
+# The kernel executes about 4.3k (FP64 instruction counters, FMA = 2).  The
 # oracle's count is reported beside the roofline as a secondary figure.
 ALG_FLOPS_PER_ORBIT_STEP = 5200.0
 KERNEL_SOURCES = ["paper_1802_00147_amd/csrc/pn_kernels.hip", "paper_1802_00147_amd/csrc/pn_device.h"]
@@ -54,11 +54,11 @@ KERNEL_SOURCES = ["paper_1802_00147_amd/csrc/pn_kernels.hip", "paper_1802_00147_
 # HBM bytes from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (KiB per dispatch,
 # scaled by a 1 GiB device copy: FETCH_SIZE x 1.9999, WRITE_SIZE x 1.0),
 # valid only for the kernel sources whose hash is recorded with them.
-# surrogate4096: the eight k_wrap_scan launches of one assisted scan, 226.4 MB
-# read + 180.1 MB written, 50.8 MB per launch; fig7: the three launches of
-# the balanced scan, 81.3 MB read + 81.2 MB written, 54.2 MB per launch.
-TRAFFIC = dict(sources_sha256="a0a398ce521ad1cbb5af85f3f6c8a6f8a0e6b93ce527798f7dad9423e4a89349",
-               bytes_per_launch={"surrogate4096": 406514885 / 8, "fig7": 162541823 / 3})
+# surrogate4096: the eight k_wrap_scan launches of one assisted scan, 223.1 MB
+# read + 181.7 MB written, 50.6 MB per launch; fig7: the three launches of
+# the balanced scan, 80.3 MB read + 86.7 MB written, 55.7 MB per launch.
+TRAFFIC = dict(sources_sha256="eea2a5fcc0a84ea97b39ca702613dca0540e6afe291c717de9305dd761ba9075",
+               bytes_per_launch={"surrogate4096": 404796651 / 8, "fig7": 166966451 / 3})
 
 
 # Table 3 of the paper: wall time of its GPU and CPU scans (seconds).
@@ -69,10 +69,10 @@ PAPER_TABLE3 = {"fig6_th1_1.571": (75.0, 1020.0), "fig7": (2213.0, 25000.0)}
 # rocprofv3 counters (SQ_INSTS_VALU_{ADD,MUL,FMA,TRANS}_F64 x 64 lanes, FMA
 # counted twice, over the launch's orbit-steps), valid only for the kernel
 # sources whose hash is recorded with them.
-HW_FLOPS = dict(sources_sha256="a0a398ce521ad1cbb5af85f3f6c8a6f8a0e6b93ce527798f7dad9423e4a89349",
-                per_orbit_step={("k_wrap_scan", "surrogate4096"): 4575.8, ("k_wrap_scan", "grid314"): 4552.4,
-                                ("k_wrap_scan", "fig7"): 4598.3, ("k_batch_scan", "batch1M"): 4582.4,
-                                ("k_fli_scan", "grid64"): 4550.4})
+HW_FLOPS = dict(sources_sha256="eea2a5fcc0a84ea97b39ca702613dca0540e6afe291c717de9305dd761ba9075",
+                per_orbit_step={("k_wrap_scan", "surrogate4096"): 4339.7, ("k_wrap_scan", "grid314"): 4338.2,
+                                ("k_wrap_scan", "fig7"): 4364.5, ("k_batch_scan", "batch1M"): 4339.9,
+                                ("k_fli_scan", "grid64"): 4338.3})
 
 
 def hardware_flops(kernel, workload):

@@ -349,8 +349,9 @@ pn_status pn_gw_polarizations(const pn_model* model, pn_params params, int64_t n
 /* Launch shape of the persistent batch kernel.  block: threads per workgroup
  * (64, 128 or 256); waves_per_simd: wavefronts per SIMD in the grid (1 or 2;
  * with PN_RK4, 2 also selects the kernel build limited to 256 registers per
- * lane so that two stay resident); chunk_steps: steps a slot runs between
- * refills (>= 1). */
+ * lane so that two stay resident); chunk_steps: the most steps a slot runs
+ * between refills (>= 1; a wavefront also stops where its first orbit ends,
+ * but a checkpointed call counts whole chunks). */
 typedef struct {
     int32_t block;
     int32_t waves_per_simd;
@@ -553,7 +554,7 @@ pn_status pn_mlp_train_step(pn_mlp* net, const float* feat, const float* label, 
  * in/out) is advanced by the steps done.  The batches' mean losses are ADDED
  * to the device scalar *loss.  order: device int32 array of nbatch * batch
  * row indices (the caller's data-loader order).  ws as for
- * pn_mlp_train_step(batch).  The first failing step's status is returned. */
+ * pn_mlp_train_step(batch); it holds the last step's tensors afterwards.  The first failing step's status is returned. */
 pn_status pn_mlp_train(pn_mlp* net, int32_t* adam_step, const float* feat, const float* label,
                        const float* target, const int32_t* order, int64_t nbatch, int32_t batch,
                        float lr, float* loss, void* ws, size_t ws_bytes, hipStream_t stream);

@@ -369,7 +369,7 @@ __device__ __forceinline__ void pair_begin(PairState& ps, const PnCoef& k, bool 
 // a radius leaves its bounds.  RK4 with six integrals: 1,383 FP64 instructions
 // a step in the loop (1,443 with both formed again and a general first Newton
 // iteration); 4,096 orbits, 5,000 steps: 14.19 ms (15.26), 98,596 orbits, 4,000
-// steps: 41.7 ms (44.1).
+// steps: 41.7 ms (44.1); 13.6 and 35.1 with what is described below.
 // Wavefront priority: of two wavefronts on a SIMD the older one issues
 // whenever it can, so the younger one would wait until it has ended and then
 // run alone, with nobody to fill the cycles in which its own results are

@@ -322,7 +322,7 @@ constexpr int kTrainFT = 16;        // rows of a training tile
 //    the loss's value comes after everything that another wavefront waits for;
 //  - ReLU masks stay in the lane that formed the activation.
 // 25 us at 2,048 rows before (weights row-major, loss on one wavefront with
-// a barrier on each side), 13 now.
+// a barrier on each side), 11 now, and 13.4 where the row-major copies are kept.
 template <bool KEEP>
 __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
     constexpr int FT = kTrainFT;
