@@ -57,7 +57,7 @@ KERNEL_SOURCES = ["paper_1802_00147_amd/csrc/pn_kernels.hip", "paper_1802_00147_
 # surrogate4096: the eight k_wrap_scan launches of one assisted scan, 223.1 MB
 # read + 181.7 MB written, 50.6 MB per launch; fig7: the three launches of
 # the balanced scan, 80.3 MB read + 86.7 MB written, 55.7 MB per launch.
-TRAFFIC = dict(sources_sha256="eea2a5fcc0a84ea97b39ca702613dca0540e6afe291c717de9305dd761ba9075",
+TRAFFIC = dict(sources_sha256="a32330481765727ae610e4eef6205476be401dfbc19ffa2f761c48ec28efe94d",
                bytes_per_launch={"surrogate4096": 404796651 / 8, "fig7": 166966451 / 3})
 
 
@@ -69,7 +69,7 @@ PAPER_TABLE3 = {"fig6_th1_1.571": (75.0, 1020.0), "fig7": (2213.0, 25000.0)}
 # rocprofv3 counters (SQ_INSTS_VALU_{ADD,MUL,FMA,TRANS}_F64 x 64 lanes, FMA
 # counted twice, over the launch's orbit-steps), valid only for the kernel
 # sources whose hash is recorded with them.
-HW_FLOPS = dict(sources_sha256="eea2a5fcc0a84ea97b39ca702613dca0540e6afe291c717de9305dd761ba9075",
+HW_FLOPS = dict(sources_sha256="a32330481765727ae610e4eef6205476be401dfbc19ffa2f761c48ec28efe94d",
                 per_orbit_step={("k_wrap_scan", "surrogate4096"): 4339.7, ("k_wrap_scan", "grid314"): 4338.2,
                                 ("k_wrap_scan", "fig7"): 4364.5, ("k_batch_scan", "batch1M"): 4339.9,
                                 ("k_fli_scan", "grid64"): 4338.3})

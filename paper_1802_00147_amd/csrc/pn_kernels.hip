@@ -723,10 +723,12 @@ struct CkptArgs {
 };
 
 // Persistent kernel: every wavefront keeps 32 orbit slots busy.  Between
-// chunks of `chunk` steps, pairs whose orbit has ended write its results and
-// claim the next queue position (one atomic per wavefront), so long orbits,
-// started first, overlap with the short ones that fill the tail.  The
-// wavefront leaves when the queue is drained and all its slots are empty.
+// runs of at most `chunk` steps (wave_run; with CKPT always `chunk`), pairs
+// whose orbit has ended write its results and claim the next queue position
+// (one atomic per wavefront), so long orbits, started first, overlap with the
+// short ones that fill the tail.  The wavefront leaves when the queue is
+// drained and all its slots are empty; 16 orbits of up to 1,000 steps, whose
+// empty slots mirror the others (kFullLanes), 3.26 -> 2.84 ms.
 // With CKPT, slots are first refilled from the orbits a previous launch
 // saved, and after ck.max_chunks chunks (if > 0) every pair still running
 // saves its state and the wavefront leaves.
