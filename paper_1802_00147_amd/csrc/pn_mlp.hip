@@ -1413,13 +1413,11 @@ pn_status train_step(pn_mlp* net, const float* feat, const float* label, const f
     if (fresh)
         hipLaunchKernelGGL(k_pack_weights, dim3(520), dim3(256), 0, stream, net->wb[0], net->wb[1], net->wb[2], u.w0p,
                            u.wf[0], u.wf[1], u.wt[0], u.wt[1]);
-    // The tensors go out row-major for the caller (keep), and also where the tiles
-    // come close to one per CU: there the loads of all workgroups meet, and the
-    // stores between them cost nothing (16 steps, with and without: batch 2,048
-    // 326 and 312 us, 3,072 385 and 375, 3,584 403 and 407, 4,096 421 and 424, 8,192 658
-    // and 645).
-    const int tiles = (int)blocks_for(B, kTrainFT);
-    if (keep || (4 * (int64_t)tiles > 3 * ncu && tiles <= ncu))
+    // The tensors go out row-major only where the caller can read them: 16 steps
+    // with and without these stores, batch 2,048 326 and 312 us, 8,192 658 and 645
+    // (4,096, one tile per CU, 418 and 427: no reason to write what nobody reads).
+    const unsigned tiles = blocks_for(B, kTrainFT);
+    if (keep)
         hipLaunchKernelGGL(k_mlp_train<true>, dim3(tiles), dim3(512), 0, stream, io);
     else
         hipLaunchKernelGGL(k_mlp_train<false>, dim3(tiles), dim3(512), 0, stream, io);
