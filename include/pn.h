@@ -519,7 +519,8 @@ pn_status pn_mlp_features(pn_params params, int64_t n, const double* r0, const d
 pn_status pn_mlp_targets(const double* fli, const int8_t* label, const double* t_end, double t_end_all,
                          int64_t n, float* lab, float* target, hipStream_t stream);
 
-/* Bytes of workspace for one training step of `batch` samples. */
+/* Bytes of workspace for one training step of `batch` samples: the tensors of
+ * pn_mlp_train_workspace_layout and a fixed 17,576,960 bytes. */
 size_t pn_mlp_train_workspace_size(int32_t batch);
 
 /* Byte offsets inside a pn_mlp_train_step workspace (of the same batch) of
@@ -554,7 +555,8 @@ pn_status pn_mlp_train_step(pn_mlp* net, const float* feat, const float* label, 
  * in/out) is advanced by the steps done.  The batches' mean losses are ADDED
  * to the device scalar *loss.  order: device int32 array of nbatch * batch
  * row indices (the caller's data-loader order).  ws as for
- * pn_mlp_train_step(batch); it holds the last step's tensors afterwards.  The first failing step's status is returned. */
+ * pn_mlp_train_step(batch); it holds the last step's tensors afterwards.  The
+ * first failing step's status is returned. */
 pn_status pn_mlp_train(pn_mlp* net, int32_t* adam_step, const float* feat, const float* label,
                        const float* target, const int32_t* order, int64_t nbatch, int32_t batch,
                        float lr, float* loss, void* ws, size_t ws_bytes, hipStream_t stream);

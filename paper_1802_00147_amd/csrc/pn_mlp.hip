@@ -269,14 +269,23 @@ __device__ __forceinline__ bf16x8 load_frag(const uint16_t* F, int cb, int sl, i
 // and its gradient with respect to the two outputs in gout [n][2]; the layer
 // gradients g3 = (g4 W4) * (h3 > 0), g2 = (g3 W3) * (h2 > 0) and g1 = (g2 W2) * (h1 > 0)
 // in g_out[2], [1], [0] [n][256] (all bfloat16).  The same tensors go out a
-// second time in row-block order, element (r, c) of C columns at
-// ((r / 8) C + c) 8 + r % 8, with zeros in the rows from n up to the next multiple
-// of 32: there the eight rows that a lane of the weight gradients' products
-// takes lie together.  Only that copy is read; the row-major one is what a step
-// leaves for its caller, and without KEEP (a step whose workspace the next one
-// overwrites) it is not written.  Hidden weights come in fragment order: wf[0], wf[1] =
+// second time in row-block order (Blocks).  Only that copy is read; the row-major
+// one is what a step leaves for its caller, and without KEEP it is not written.
+// out may be null.  Hidden weights come in fragment order: wf[0], wf[1] =
 // W2, W3 (columns: outputs), wt[0], wt[1] = W2, W3 transposed (columns: inputs);
 // W1 comes with its rows padded to eight values.
+// A bfloat16 tensor of n rows and C columns in row-block order: element (r, c) of
+// a slice of 32 rows at ((r / 8) C + c) 8 + r % 8, so that the eight rows which a
+// lane of the weight gradients' products takes lie together.  The n / 32 whole
+// slices lie one behind the other at `full`; the rest of the rows, if any, are a
+// slice of their own at `last`, with zeros in the rows from n on.  (Eight whole
+// rows take the same bytes in this order as in row-major order: `full` may be the
+// place of the row-major tensor, in which the slice at `last` would not fit.)
+struct Blocks {
+    uint16_t* full;
+    uint16_t* last;
+};
+
 struct TrainIO {
     const uint16_t* w0;              // layer 1 [256][8]
     const uint16_t* w3;              // layer 4 [2][256]
@@ -294,10 +303,7 @@ struct TrainIO {
     uint16_t* h_out[3];
     uint16_t* gout;
     uint16_t* g_out[3];
-    uint16_t* xT;                    // row-block order
-    uint16_t* hT[3];
-    uint16_t* g4T;
-    uint16_t* gT[3];
+    Blocks xT, hT[3], g4T, gT[3];
 };
 
 constexpr int kTrainFT = 16;        // rows of a training tile
@@ -337,6 +343,9 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
     const int64_t n = io.n;
     const int64_t tile = blockIdx.x, ntiles = gridDim.x;
     const int64_t r0 = tile * FT;
+    const bool part = (r0 >> 5) >= (n >> 5);          // the tile is in the slice that ends past n
+    // This tile's rows in a tensor of C columns in row-block order.
+    auto rows_of = [&](const Blocks& t, int C) { return part ? t.last + (r0 & 31) * C : t.full + r0 * C; };
     const bool live = r0 + lr < n;                    // rows past n repeat row n - 1 and are never stored
     const int32_t src = io.idx[live ? r0 + lr : n - 1];
     const uint16_t w4v = io.w3[tid];                  // 512 threads, 2 x 256 weights
@@ -385,8 +394,8 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
     // One tensor's columns of this wavefront: row-major through LDS (where
     // the next product reads it, too) and in row-block order.  The LDS
     // reads are of what this wavefront has just written, in order.
-    auto put = [&](uint16_t (*h)[FLD], const uint16_t (&y)[2][4], uint16_t* dst, uint16_t* dstT) {
-        char* T = reinterpret_cast<char*>(dstT + (r0 * 256 + c0 * 8));       // the same in all lanes
+    auto put = [&](uint16_t (*h)[FLD], const uint16_t (&y)[2][4], uint16_t* dst, const Blocks& dstT) {
+        char* T = reinterpret_cast<char*>(rows_of(dstT, 256) + c0 * 8);      // the same in all lanes
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
 #pragma unroll
@@ -450,7 +459,7 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
         for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wf0[j], acc[j], 0, 0, 0);
         if (wave == 0 && lq == 0) {
             if (live && KEEP) *reinterpret_cast<bf16x8*>(io.x_out + (r0 + lr) * kFeatLd) = a;
-            uint16_t* T = io.xT + (r0 / 8 + (lr >> 3)) * kFeatLd * 8 + (lr & 7);
+            uint16_t* T = rows_of(io.xT, kFeatLd) + (lr >> 3) * kFeatLd * 8 + (lr & 7);
 #pragma unroll
             for (int t = 0; t < 8; ++t) T[8 * t] = live ? v[t] : (uint16_t)0;
             if (pad)
@@ -532,12 +541,11 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
                 const float z = o[0], f = o[1], d = f - tgt;
                 l = fmaxf(z, 0.0f) - lab * z + log1pf(expf(-fabsf(z)));
                 l += fabsf(d) <= 1.0f ? 0.5f * d * d : fabsf(d) - 0.5f;
-                if (KEEP) {
-                    *reinterpret_cast<float2*>(io.out + 2 * (r0 + lr)) = make_float2(z, f);
+                if (io.out) *reinterpret_cast<float2*>(io.out + 2 * (r0 + lr)) = make_float2(z, f);
+                if (KEEP)
                     *reinterpret_cast<uint32_t*>(io.gout + 2 * (r0 + lr)) = (uint32_t)g40 | ((uint32_t)g41 << 16);
-                }
             }
-            uint16_t* T = io.g4T + (r0 / 8 + (lr >> 3)) * 2 * 8 + (lr & 7);
+            uint16_t* T = rows_of(io.g4T, 2) + (lr >> 3) * 2 * 8 + (lr & 7);
             T[0] = g40;
             T[8] = g41;
             if (pad) T[2 * 2 * 8] = T[2 * 2 * 8 + 8] = 0;
@@ -811,9 +819,9 @@ __global__ __launch_bounds__(512) void k_mlp_infer(const uint16_t* __restrict__ 
 // and bias gradients (column sums of g_l) over the batch rows, and the Adam
 // update of the elements they belong to, with the bfloat16 copies.
 struct UpdateArgs {
-    const uint16_t* g[4];   // g1 .. g4 in row-block order (256, 256, 256, 2 columns)
-    const uint16_t* a[4];   // X, h1, h2, h3 in row-block order (8, 256, 256, 256 columns)
-    int blocks8;            // 8-row blocks (a multiple of 4)
+    Blocks g[4];            // g1 .. g4 (256, 256, 256, 2 columns)
+    Blocks a[4];            // X, h1, h2, h3 (8, 256, 256, 256 columns)
+    int full, slices;       // whole slices, and all
     int chunk[4];           // 32-row slices of a split of layer l's sums
     int splits[4];
     float *w[4], *mw[4], *vw[4];
@@ -884,12 +892,12 @@ constexpr int kHiddenTiles = 64;    // 32 x 32 tiles of a hidden weight
 // Layer l's gradient of the 16 MB x 16 NB tile at (m0, n0): wavefront w sums
 // split w (and w + 16, ..), the partials meet in LDS, and thread t returns
 // element (t / 32, t % 32) summed over the splits in increasing order.
-template <int MB, int NB>
+template <int MB, int NB, bool APART>
 __device__ __forceinline__ float tile_gradient(const UpdateArgs& u, int l, int cg, int m0, int ca, int n0,
                                                float (*part)[32 * kPartLd]) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int lr = lane & 15, lq = lane >> 4;
-    const int slices = u.blocks8 / 4, chunk = u.chunk[l], splits = u.splits[l];
+    const int slices = u.slices, chunk = u.chunk[l], splits = u.splits[l];
     const int r = tid >> 5, c = tid & 31;
     float x = 0.0f;
     for (int z0 = 0; z0 < splits; z0 += kUpWaves) {
@@ -901,7 +909,9 @@ __device__ __forceinline__ float tile_gradient(const UpdateArgs& u, int l, int c
 #pragma unroll
                 for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
             const int s1 = (z + 1) * chunk < slices ? (z + 1) * chunk : slices;
-            slice_sums<MB, NB>(u.g[l], cg, m0, u.a[l], ca, n0, z * chunk, s1, lane, acc);
+            slice_sums<MB, NB>(u.g[l].full, cg, m0, u.a[l].full, ca, n0, z * chunk, APART && s1 > u.full ? u.full : s1,
+                               lane, acc);
+            if (APART && s1 > u.full) slice_sums<MB, NB>(u.g[l].last, cg, m0, u.a[l].last, ca, n0, 0, 1, lane, acc);
 #pragma unroll
             for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -934,6 +944,9 @@ __device__ __forceinline__ float tile_gradient(const UpdateArgs& u, int l, int c
 // operands instead of 2.
 constexpr int kUpW1 = 2 * kHiddenTiles, kUpW4 = kUpW1 + 8, kUpBias = kUpW4 + 8, kUpBlocks = kUpBias + 25;
 
+// APART: the last slice, not whole, is apart from the others (a choice of address
+// per slice instead took 20% more at 8,200 rows: fewer loads in flight).
+template <bool APART>
 __global__ __launch_bounds__(1024) void k_mlp_update(UpdateArgs u) {
     __shared__ __attribute__((aligned(16))) float part[kUpWaves][32 * kPartLd];
     __shared__ __attribute__((aligned(16))) uint16_t tile[32][40];
@@ -943,7 +956,7 @@ __global__ __launch_bounds__(1024) void k_mlp_update(UpdateArgs u) {
         const int x = b & 7, q = b >> 3;                 // XCD, tile of its 4 x 4 block
         const int l = 1 + (x >> 2);
         const int m0 = 32 * (4 * (x & 1) + (q & 3)), n0 = 32 * (4 * ((x >> 1) & 1) + (q >> 2));
-        const float g = tile_gradient<2, 2>(u, l, 256, m0, 256, n0, part);
+        const float g = tile_gradient<2, 2, APART>(u, l, 256, m0, 256, n0, part);
         const int64_t e = (int64_t)(m0 + r) * 256 + n0 + c;
         const uint16_t y = f2bf(adam(g, u.w[l], u.mw[l], u.vw[l], e, u.lr, u.c1, u.c2));
         u.wb[l][e] = y;
@@ -965,8 +978,8 @@ __global__ __launch_bounds__(1024) void k_mlp_update(UpdateArgs u) {
     if (b < kUpBias) {
         const bool first = b < kUpW4;
         const int k = 32 * (first ? b - kUpW1 : b - kUpW4), l = first ? 0 : 3;
-        const float g = first ? tile_gradient<2, 1>(u, 0, 256, k, kFeatLd, 0, part)
-                              : tile_gradient<1, 2>(u, 3, 2, 0, 256, k, part);
+        const float g = first ? tile_gradient<2, 1, APART>(u, 0, 256, k, kFeatLd, 0, part)
+                              : tile_gradient<1, 2, APART>(u, 3, 2, 0, 256, k, part);
         if (first ? c < 7 : r < 2) {
             const int64_t e = first ? (int64_t)(k + r) * 7 + c : (int64_t)r * 256 + k + c;
             const uint16_t y = f2bf(adam(g, u.w[l], u.mw[l], u.vw[l], e, u.lr, u.c1, u.c2));
@@ -979,13 +992,18 @@ __global__ __launch_bounds__(1024) void k_mlp_update(UpdateArgs u) {
     // sum per t < 8, and the 256 sums of a column meet pairwise, halves first.
     const int l = (b - kUpBias) >> 3, n0 = 32 * ((b - kUpBias) & 7), cols = kOut[l];
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (n0 + c < cols)
-        for (int rb = r; rb < u.blocks8; rb += 32) {
+    if (n0 + c < cols) {
+        auto add = [&](const uint16_t* G, int64_t rb) {
             union { bf16x8 v; uint16_t e[8]; } p;
-            p.v = load_bf16x8(u.g[l] + ((int64_t)rb * cols + n0 + c) * 8);
+            p.v = load_bf16x8(G + (rb * cols + n0 + c) * 8);
 #pragma unroll
             for (int t = 0; t < 8; ++t) s[t] += bf2f(p.e[t]);
-        }
+        };
+        const int end = 4 * (APART ? u.full : u.slices);
+        int rb = r;
+        for (; rb < end; rb += 32) add(u.g[l].full, rb);
+        if (APART && rb < end + 4) add(u.g[l].last, rb - end);
+    }
     float (*half)[32][8] = reinterpret_cast<float (*)[32][8]>(&part[0][0]);
     for (int k = 16; k > 0; k >>= 1) {
         if (r >= k && r < 2 * k)
@@ -1004,6 +1022,39 @@ __global__ __launch_bounds__(1024) void k_mlp_update(UpdateArgs u) {
             for (int t = 0; t < k; ++t) s[t] += s[t + k];
         adam(s[0], u.b[l], u.mb[l], u.vb[l], n0 + c, u.lr, u.c1, u.c2);
     }
+}
+
+// The tensors of a step in row-major order, dst, from their row-block order, whose
+// whole slices lie in dst itself: eight rows take the same bytes in both orders, so
+// a workgroup reads 2,048 elements of whole 8-row blocks, exchanges them in LDS and
+// writes them to the same place (those of the slice at `last`: to its rows in dst).
+// Grid (8-row blocks of 256 columns, tensors); 8,192 rows: 25 MB each way.
+struct RowMajorArgs {
+    Blocks t[8];
+    uint16_t* dst[8];
+    int cols[8];            // powers of two, at most 256
+    int64_t n;
+};
+
+__global__ __launch_bounds__(256) void k_row_major(RowMajorArgs p) {
+    __shared__ __attribute__((aligned(16))) uint16_t tile[2048];
+    const int k = blockIdx.y, tid = threadIdx.x, C = p.cols[k];
+    const int64_t total = p.n * C, base = (int64_t)blockIdx.x * 2048;
+    if (base >= total) return;                        // the same in all threads
+    const int64_t full = (p.n >> 5) * 32 * C;         // elements of the whole slices
+    const int64_t e = base + 8 * tid;                 // this thread's column of an 8-row block
+    if (e < (p.n + 7) / 8 * 8 * C) {
+        union { uint4 v; uint16_t e[8]; } u;
+        u.v = *reinterpret_cast<const uint4*>(e < full ? p.t[k].full + e : p.t[k].last + (e - full));
+        const int g = tid / C, c = tid % C;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) tile[(8 * g + r) * C + c] = u.e[r];
+    }
+    __syncthreads();
+    if (e + 8 <= total)
+        *reinterpret_cast<uint4*>(p.dst[k] + e) = *reinterpret_cast<const uint4*>(&tile[8 * tid]);
+    else
+        for (int r = 0; r < 8 && e + r < total; ++r) p.dst[k][e + r] = tile[8 * tid + r];
 }
 
 // The training pass's copies of the weights (grid 520 x 256 threads: one
@@ -1248,6 +1299,17 @@ size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 size_t rows32(int batch) { return ((size_t)batch + 31) / 32 * 32; }
 
+// Bytes of a training workspace behind the reported tensors, the same for every
+// batch (callers keep workspaces of this size).
+constexpr size_t kStepRoom = 17576960;
+
+// Whether the row-block tensors of a step have room behind the reported ones (up
+// to 5,504 rows).  Otherwise they take those tensors' places.
+bool blocks_apart(int batch) {
+    const size_t R = rows32(batch);
+    return al(R * kFeatLd * 2) + 6 * al(R * 256 * 2) + al(R * 2 * 2) + 4 * al(256 * 256 * 2) + al(256 * 8 * 2) <= kStepRoom;
+}
+
 bool net_ok(const pn_mlp* net, bool training) {
     if (!net) return false;
     for (int l = 0; l < 4; ++l) {
@@ -1295,14 +1357,8 @@ size_t pn_mlp_param_count(int32_t layer, int32_t which) {
 
 size_t pn_mlp_train_workspace_size(int32_t batch) {
     if (batch <= 0) return 0;
-    const size_t B = (size_t)batch, R = rows32(batch);
-    const size_t own = al(R * kFeatLd * 2) + 6 * al(R * 256 * 2) + al(R * 2 * 2) + 4 * al(256 * 256 * 2) + al(256 * 8 * 2);
-    // The interface promises room for FP32 gradients, four 4 MB buffers and two
-    // transposed weights behind the reported tensors; up to about 5500 rows the
-    // step's own buffers are smaller than that.
-    const size_t promised = (2 * 256 * 256 + 256 * 7 + 2 * 256 + 4 * 256) * 4 + 4 * ((size_t)1 << 22) + 2 * 256 * 256 * 2;
-    return al(B * kFeatLd * 2) + 3 * al(B * 256 * 2) + al(B * 2 * 4) + al(B * 2 * 2) + 3 * al(B * 256 * 2) +
-           (own > promised ? own : promised);
+    const size_t B = (size_t)batch;
+    return al(B * kFeatLd * 2) + 3 * al(B * 256 * 2) + al(B * 2 * 4) + al(B * 2 * 2) + 3 * al(B * 256 * 2) + kStepRoom;
 }
 
 pn_status pn_mlp_train_workspace_layout(int32_t batch, size_t* off) {
@@ -1352,7 +1408,12 @@ void gradient_splits(int l, int batch, int& chunk, int& splits) {
 // tensors in row-block order and bfloat16 copies of W2 and W3, straight and
 // transposed, in fragment order; each update rewrites the copies with the
 // bfloat16 weights, so a run of steps on one workspace forms them once (fresh)
-// before its first step.
+// before its first step.  keep: the caller can read the step's tensors.  Where the
+// row-block tensors lie in the places of the row-major ones (blocks_apart), these
+// are formed from them at the end.  That costs a launch, in a step whose tensors
+// are kept only, and saves the second place: a single step of 8,192 rows 51.5 ->
+// 61.8 us and a workspace of 51.3 -> 43.0 MB, of 65,536 rows 295 -> 299 us and 406 ->
+// 221 MB; 16 steps of one call 655 -> 659 and 3,734 -> 3,712 us.
 pn_status train_step(pn_mlp* net, const float* feat, const float* label, const float* target, const int32_t* idx,
                      int32_t batch, int32_t step, float lr, float* loss, void* ws, size_t ws_bytes,
                      hipStream_t stream, bool fresh, bool keep) {
@@ -1373,34 +1434,39 @@ pn_status train_step(pn_mlp* net, const float* feat, const float* label, const f
     char* const w0 = static_cast<char*>(ws);
     char* p = w0 + off[8] + al((size_t)B * 256 * 2);
     auto take = [&](size_t elements) { uint16_t* q = (uint16_t*)p; p += al(2 * elements); return q; };
+    const bool apart = blocks_apart(B);
+    const int full = B / 32;
     const size_t R = rows32(B);
+    // Tensor at offset o of the workspace with C columns, in row-block order.
+    auto blocks = [&](size_t o, int C) {
+        if (!apart) return Blocks{(uint16_t*)(w0 + o), take(32 * (size_t)C)};
+        uint16_t* const t = take(R * C);
+        return Blocks{t, t + (size_t)full * 32 * C};
+    };
     TrainIO io;
     UpdateArgs u;
     io.w3 = net->wb[3];
     io.feat = feat; io.label = label; io.target = target; io.idx = idx;
     io.n = B;
-    io.out = (float*)(w0 + off[4]);
+    io.out = keep ? (float*)(w0 + off[4]) : nullptr;
     io.loss = loss;
     io.x_out = (uint16_t*)(w0 + off[0]);
     io.gout = (uint16_t*)(w0 + off[5]);
-    io.xT = take(R * kFeatLd);
-    io.g4T = take(R * 2);
+    u.a[0] = io.xT = blocks(off[0], kFeatLd);
+    u.g[3] = io.g4T = blocks(off[5], 2);
     for (int l = 0; l < 3; ++l) {
         io.h_out[l] = (uint16_t*)(w0 + off[1 + l]);
         io.g_out[l] = (uint16_t*)(w0 + off[8 - l]);
-        io.hT[l] = take(R * 256);
-        io.gT[l] = take(R * 256);
-        u.g[l] = io.gT[l];
-        u.a[l + 1] = io.hT[l];
+        u.a[l + 1] = io.hT[l] = blocks(off[1 + l], 256);
+        u.g[l] = io.gT[l] = blocks(off[8 - l], 256);
     }
-    u.g[3] = io.g4T;
-    u.a[0] = io.xT;
     for (int t = 0; t < 2; ++t) {
         io.wf[t] = u.wf[t] = take(256 * 256);
         io.wt[t] = u.wt[t] = take(256 * 256);
     }
     io.w0 = u.w0p = take(256 * 8);
-    u.blocks8 = (int)(R / 8);
+    u.full = full;
+    u.slices = (int)(R / 32);
     for (int l = 0; l < 4; ++l) {
         io.b[l] = net->b[l];
         gradient_splits(l, B, u.chunk[l], u.splits[l]);
@@ -1413,15 +1479,24 @@ pn_status train_step(pn_mlp* net, const float* feat, const float* label, const f
     if (fresh)
         hipLaunchKernelGGL(k_pack_weights, dim3(520), dim3(256), 0, stream, net->wb[0], net->wb[1], net->wb[2], u.w0p,
                            u.wf[0], u.wf[1], u.wt[0], u.wt[1]);
-    // The tensors go out row-major only where the caller can read them: 16 steps
+    // The tensors go out row-major only where the caller can read them (keep): 16 steps
     // with and without these stores, batch 2,048 326 and 312 us, 8,192 658 and 645
     // (4,096, one tile per CU, 418 and 427: no reason to write what nobody reads).
     const unsigned tiles = blocks_for(B, kTrainFT);
-    if (keep)
+    if (keep && apart)
         hipLaunchKernelGGL(k_mlp_train<true>, dim3(tiles), dim3(512), 0, stream, io);
     else
         hipLaunchKernelGGL(k_mlp_train<false>, dim3(tiles), dim3(512), 0, stream, io);
-    hipLaunchKernelGGL(k_mlp_update, dim3(kUpBlocks), dim3(64 * kUpWaves), 0, stream, u);
+    if (apart || full == u.slices)
+        hipLaunchKernelGGL(k_mlp_update<false>, dim3(kUpBlocks), dim3(64 * kUpWaves), 0, stream, u);
+    else
+        hipLaunchKernelGGL(k_mlp_update<true>, dim3(kUpBlocks), dim3(64 * kUpWaves), 0, stream, u);
+    if (keep && !apart) {
+        RowMajorArgs r{{io.hT[0], io.hT[1], io.hT[2], io.gT[0], io.gT[1], io.gT[2], io.xT, io.g4T},
+                       {io.h_out[0], io.h_out[1], io.h_out[2], io.g_out[0], io.g_out[1], io.g_out[2], io.x_out, io.gout},
+                       {256, 256, 256, 256, 256, 256, kFeatLd, 2}, B};
+        hipLaunchKernelGGL(k_row_major, dim3(blocks_for(B, 8), 8), dim3(256), 0, stream, r);
+    }
     return launched("pn_mlp_train_step");
 }
 
