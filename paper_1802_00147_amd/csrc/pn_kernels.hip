@@ -378,9 +378,10 @@ __device__ __forceinline__ void pair_begin(PairState& ps, const PnCoef& k, bool 
 // flight to the end (an issue in 94-96% of the cycles instead of 87-89%):
 // 400,000 uneven orbits 85.2 -> 77.4 ms, 98,596 orbits, 4,000 steps, 37.4 -> 36.3;
 // low for half the step or for a dozen instructions gains nothing.
+// own: the pair is not a mirror of another one, and records its trace.
 template <int METHOD, int MODE>
 __device__ __forceinline__ void pair_step(PairState& ps, const PnCoef& k, bool shadow, const FliArgs& fa,
-                                          int64_t i) {
+                                          int64_t i, bool own) {
     bool nc;
     __builtin_amdgcn_s_setprio(1);
     if constexpr (!kPnCarriesGeom<MODE>) ps.geo = pn_rhs_geom(k, ps.y);
@@ -419,7 +420,7 @@ __device__ __forceinline__ void pair_step(PairState& ps, const PnCoef& k, bool s
         ps.d2 = pair_d2(ps.y);
     }
     const int64_t tev = fa.out.trace_every;
-    if (__builtin_expect(tev > 0, 0) && (ps.t % tev) == 0 && !shadow) {
+    if (__builtin_expect(tev > 0, 0) && (ps.t % tev) == 0 && own && !shadow) {
         const int64_t row = ps.t / tev - 1;
         if (row < fa.out.ntrace) fa.out.trace[row * fa.ld + i] = ps.acc + log10(sqrt(ps.d2) / fa.d0);
     }
@@ -554,7 +555,7 @@ __global__ __launch_bounds__(kBlock, METHOD == PN_RK4 && MODE == PN_CORR_SPIN &&
         // The pairs that run, in lockstep, until the first of them ends.
         if (pair_running(ps)) {
             const unsigned long long live = __ballot(true);
-            do pair_step<METHOD, MODE>(ps, k, shadow, fa, i);
+            do pair_step<METHOD, MODE>(ps, k, shadow, fa, i, own);
             while (__ballot(pair_running(ps)) == live);
         }
         if (own && !pair_running(ps)) {
@@ -816,7 +817,7 @@ __global__ __launch_bounds__(256, OCC) void k_batch_scan(ParamArgs pa, FliArgs f
             work = work || take;
         }
         if (work)
-            for (int c = 0; c < run && pair_running(ps); ++c) pair_step<METHOD, MODE>(ps, k, shadow, fa, i);
+            for (int c = 0; c < run && pair_running(ps); ++c) pair_step<METHOD, MODE>(ps, k, shadow, fa, i, cur >= 0);
         if (cur >= 0 && !pair_running(ps)) {
             pair_finish(ps, k, shadow, fa, cur);
             cur = -1;
@@ -1008,7 +1009,7 @@ __global__ __launch_bounds__(256, OCC) void k_wrap_scan(ParamArgs pa, FliArgs fa
         }
         if (work)
             for (int c = 0; c < run && ps.st == PN_ORBIT_OK && ps.t < stop; ++c)
-                pair_step<METHOD, MODE>(ps, k, shadow, fa, orbit);
+                pair_step<METHOD, MODE>(ps, k, shadow, fa, orbit, active);
         if (active) {
             if (!(ps.st == PN_ORBIT_OK && ps.t < stop)) {
                 if (pend > tend) {
