@@ -1388,18 +1388,14 @@ pn_status pn_mlp_sync_bf16(pn_mlp* net, hipStream_t stream) {
 namespace {
 
 // Splits of layer l's weight-gradient sums over the batch rows (32-row
-// slices per split, splits): enough that the 64 x 64 tiles of the product and
-// the splits together are up to 256 pieces of at least 128 rows.  The sums are
-// formed split by split in increasing order, so this rule is part of the
-// result.
+// slices per split, splits): from 512 rows on as many as leave each at least 128
+// rows, up to 16 for a hidden weight, one per wavefront of an update workgroup,
+// and 64 for the outer two, which have fewer workgroups to share the rows.  The
+// sums are formed split by split in increasing order, so this rule is part of
+// the result.
 void gradient_splits(int l, int batch, int& chunk, int& splits) {
-    const int64_t M = kOut[l], N = kIn[l], K = batch;
-    const int64_t tiles = (int64_t)blocks_for(N, 64) * blocks_for(M, 64);
-    int64_t sp = 1;
-    if (K >= 512) {
-        sp = std::min<int64_t>({256 / tiles, K / 128, ((int64_t)1 << 20) / (M * N)});
-        if (sp < 1) sp = 1;
-    }
+    const int64_t K = batch, most = l == 1 || l == 2 ? 16 : 64;
+    const int64_t sp = K >= 512 ? std::min(most, K / 128) : 1;
     chunk = (int)(((K + sp - 1) / sp + 31) / 32);
     splits = (int)((K + 32 * (int64_t)chunk - 1) / (32 * (int64_t)chunk));
 }
