@@ -31,12 +31,17 @@ namespace {
 
 constexpr int kBlock = 64;  // one wavefront per workgroup
 
-// Lanes of a wavefront that have to be at work for full speed.  Where a CU has
-// no more than 32 lanes in FP64 work, its vector instructions wait: one orbit
-// takes 640 to 885 us for 256 RK4 steps, depending on the XCD it lands on, 33 or
-// 64 equal ones always 640; with one or two lanes in every wavefront of a full
-// chip a step takes four times as long as with all of them.  Lanes without an
-// orbit of their own therefore mirror one until that many are at work.
+// Lanes of a wavefront that are kept at work.  Where the wavefronts that a CU's
+// four SIMDs issue from together have no more than 32 lanes in FP64 work, its
+// vector instructions wait.  Without mirrors 64 or 256 wavefronts of 1,000 RK4 steps
+// took 4.07 ms with 32 lanes at work in each and 3.08 with 34; 1,024, four to a CU,
+// 11.8 ms with 8 lanes in each and 3.1 with 10; one wavefront of 256 steps 750 to
+// 1,000 us, by XCD, with up to 32 lanes and always 753 with 33 or more.  A wavefront
+// cannot tell what else its CU runs, so each keeps enough lanes for all four: those
+// without an orbit of their own mirror one.  Beside other wavefronts the mirrors are
+// more than the rule asks for, at no cost (an instruction takes the same cycles
+// for any number of lanes): the runs above now take the same time, within 1%, with 2
+// and with 64 lanes.
 constexpr int kFullLanes = 34;
 
 void set_error(const char* what, hipError_t e) { pn_detail::set_last_error(what, hipGetErrorString(e)); }
@@ -441,7 +446,7 @@ __device__ __forceinline__ bool lane_mirrors(unsigned long long live, bool idle)
 
 // Copies the first live pair's trajectory (parameters, state, position) into
 // the lanes with `take`.  What only pair_finish reads is left out: a mirror
-// ends with its source and reports nothing.
+// ends with its source and reports nothing, trace rows included (pair_step's own).
 template <bool SHARED>
 __device__ __forceinline__ void pair_mirror(PairState& ps, PnCoef& k, int64_t& i, unsigned long long live,
                                             bool take) {

@@ -328,8 +328,11 @@ constexpr int kTrainFT = 16;        // rows of a training tile
 //    the loss's value comes after everything that another wavefront waits for;
 //  - ReLU masks stay in the lane that formed the activation.
 // 25 us at 2,048 rows before (weights row-major, loss on one wavefront with
-// a barrier on each side), 11 now, and 13.4 where the row-major copies are kept.
-template <bool KEEP>
+// a barrier on each side), 13.0 now (median of 57; 11.7 at the least), and 14.0 where
+// the row-major copies are kept.  The wavefronts wait for memory or at barriers in
+// 45% of their cycles, to issue in 32%, and an MFMA is in flight in 12%.
+// APART: the last slice, not whole, is apart from the others.
+template <bool KEEP, bool APART>
 __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
     constexpr int FT = kTrainFT;
     __shared__ __attribute__((aligned(16))) uint16_t h1s[FT][FLD];
@@ -343,7 +346,7 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
     const int64_t n = io.n;
     const int64_t tile = blockIdx.x, ntiles = gridDim.x;
     const int64_t r0 = tile * FT;
-    const bool part = (r0 >> 5) >= (n >> 5);          // the tile is in the slice that ends past n
+    const bool part = APART && (r0 >> 5) >= (n >> 5); // the tile is in the slice at `last`
     // This tile's rows in a tensor of C columns in row-block order.
     auto rows_of = [&](const Blocks& t, int C) { return part ? t.last + (r0 & 31) * C : t.full + r0 * C; };
     const bool live = r0 + lr < n;                    // rows past n repeat row n - 1 and are never stored
@@ -575,8 +578,8 @@ __global__ __launch_bounds__(512) void k_mlp_train(TrainIO io) {
 // first half written in one step, the second in the next, read in the third)
 // and two more steps at the end.  4,194,304 rows: 859 us with two buffers and
 // unordered groups (58% of the cycles with an MFMA in flight), 799 now (68%).
-// The clock falls from 2.31 to 2.11 GHz as the cores fill, so fewer cycles
-// shorten the time by less: from here power bounds the kernel.
+// The clock under this load is lower, 2.1 GHz instead of 2.3, so fewer cycles
+// shorten the time by less.
 // Products, K-slice order, bias-started accumulators and the bfloat16 ReLU
 // epilogue are those of k_gemm_bf16: the outputs equal the
 // layer-by-layer path bit for bit.
@@ -937,7 +940,7 @@ __device__ __forceinline__ float tile_gradient(const UpdateArgs& u, int l, int c
 // hidden layer, one for the output layer).  A tile is complete in its
 // workgroup, so its Adam update follows at once: no partial sums in memory and
 // no second launch (before: 15.7 us for the products with split partials of 8 MB,
-// 8.5 us for Adam, at 2,048 rows; 6.1 us together now).  Bound by the operands'
+// 8.5 us for Adam, at 2,048 rows; 6.8 us together now).  Bound by the operands'
 // way from the other XCDs' L2 and by latency: 16 wavefronts keep 16 KB each in
 // flight.  Consecutive workgroups go to different XCDs, so workgroup b takes its
 // tile from the 4 x 4 block of tiles of XCD b % 8, which reads 1 MB of
@@ -1409,7 +1412,7 @@ void gradient_splits(int l, int batch, int& chunk, int& splits) {
 // are formed from them at the end.  That costs a launch, in a step whose tensors
 // are kept only, and saves the second place: a single step of 8,192 rows 51.5 ->
 // 61.8 us and a workspace of 51.3 -> 43.0 MB, of 65,536 rows 295 -> 299 us and 406 ->
-// 221 MB; 16 steps of one call 655 -> 659 and 3,734 -> 3,712 us.
+// 221 MB; 16 steps of one call 649 -> 653 and 3,734 -> 3,712 us.
 pn_status train_step(pn_mlp* net, const float* feat, const float* label, const float* target, const int32_t* idx,
                      int32_t batch, int32_t step, float lr, float* loss, void* ws, size_t ws_bytes,
                      hipStream_t stream, bool fresh, bool keep) {
@@ -1479,14 +1482,16 @@ pn_status train_step(pn_mlp* net, const float* feat, const float* label, const f
     // with and without these stores, batch 2,048 326 and 312 us, 8,192 658 and 645
     // (4,096, one tile per CU, 418 and 427: no reason to write what nobody reads).
     const unsigned tiles = blocks_for(B, kTrainFT);
-    if (keep && apart)
-        hipLaunchKernelGGL(k_mlp_train<true>, dim3(tiles), dim3(512), 0, stream, io);
-    else
-        hipLaunchKernelGGL(k_mlp_train<false>, dim3(tiles), dim3(512), 0, stream, io);
-    if (apart || full == u.slices)
+    if (apart || full == u.slices) {
+        if (keep && apart)
+            hipLaunchKernelGGL((k_mlp_train<true, false>), dim3(tiles), dim3(512), 0, stream, io);
+        else
+            hipLaunchKernelGGL((k_mlp_train<false, false>), dim3(tiles), dim3(512), 0, stream, io);
         hipLaunchKernelGGL(k_mlp_update<false>, dim3(kUpBlocks), dim3(64 * kUpWaves), 0, stream, u);
-    else
+    } else {
+        hipLaunchKernelGGL((k_mlp_train<false, true>), dim3(tiles), dim3(512), 0, stream, io);
         hipLaunchKernelGGL(k_mlp_update<true>, dim3(kUpBlocks), dim3(64 * kUpWaves), 0, stream, u);
+    }
     if (keep && !apart) {
         RowMajorArgs r{{io.hT[0], io.hT[1], io.hT[2], io.gT[0], io.gT[1], io.gT[2], io.xT, io.g4T},
                        {io.h_out[0], io.h_out[1], io.h_out[2], io.g_out[0], io.g_out[1], io.g_out[2], io.x_out, io.gout},
