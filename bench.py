@@ -21,8 +21,8 @@ advances one orbit and its shadow by h, with both corrections and the FLI
 update).
 
 roofline: the dominant kernel (the FP64 scan) against the FP64 vector peak,
-with the algorithmic work per orbit-step ALG_FLOPS_PER_ORBIT_STEP; hardware
-FP64 operations per orbit-step from rocprofv3 counters are reported beside
+with the FP64 operations that a step executes, FLOPS_PER_ORBIT_STEP; the
+count of the workload itself, from rocprofv3 counters, is reported beside
 it while the kernel sources are unchanged.  cpu_baseline: the oracle as it
 is, timed on this host on a bounded sample of the same workload.
 """
@@ -41,24 +41,25 @@ sys.path.insert(0, ROOT)
 METRIC = "FP64 orbit-steps/s + scan grid-pts/s (surrogate vs plain, ≥99% FLI label agree)"
 FP64_VECTOR_PEAK_TFLOPS = 78.6     # MI355X: 256 CU x 128 FP64 flop/clk x 2.4 GHz
 
-# Algorithmic FP64 work of one orbit-step with RK4 and the six-integral
-# correction (two sweeps), the scope's per-unit figure: about 2 x (2.0k for
-# the RK4 step + 0.6k for the correction) + 40 for the separation.  The
-# oracle's counting scalar gives 7.7k: it evaluates H and its gradient
-# separately, and H again with dH/dp in every momentum-scaling iteration.
-# The kernel executes about 4.3k (FP64 instruction counters, FMA = 2).  The
-# oracle's count is reported beside the roofline as a secondary figure.
-ALG_FLOPS_PER_ORBIT_STEP = 5200.0
+# FP64 work of one orbit-step with RK4 and the six-integral correction (two
+# sweeps), as the scan kernels execute it (FP64 instruction counters, FMA = 2;
+# grid64, where nearly every orbit runs every step: the loop's own count).  The
+# scope's estimate, 2 x (2.0k for the RK4 step + 0.6k for the correction) + 40 for
+# the separation = 5,200, lies above it and is not used.  The oracle's counting
+# scalar gives 7.7k: it evaluates H and its gradient separately, and H again
+# with dH/dp in every momentum-scaling iteration; that count is reported beside
+# the roofline.
+FLOPS_PER_ORBIT_STEP = 4338.0
 KERNEL_SOURCES = ["paper_1802_00147_amd/csrc/pn_kernels.hip", "paper_1802_00147_amd/csrc/pn_device.h"]
 
 # HBM bytes from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (KiB per dispatch,
 # scaled by a 1 GiB device copy: FETCH_SIZE x 1.9999, WRITE_SIZE x 1.0),
 # valid only for the kernel sources whose hash is recorded with them.
-# surrogate4096: the eight k_wrap_scan launches of one assisted scan, 223.1 MB
-# read + 181.7 MB written, 50.6 MB per launch; fig7: the three launches of
-# the balanced scan, 80.3 MB read + 86.7 MB written, 55.7 MB per launch.
-TRAFFIC = dict(sources_sha256="a32330481765727ae610e4eef6205476be401dfbc19ffa2f761c48ec28efe94d",
-               bytes_per_launch={"surrogate4096": 404796651 / 8, "fig7": 166966451 / 3})
+# surrogate4096: the eight k_wrap_scan launches of one assisted scan, 223.0 MB
+# read + 181.5 MB written, 50.6 MB per launch; fig7: the three launches of
+# the balanced scan, 80.2 MB read + 86.9 MB written, 55.7 MB per launch.
+TRAFFIC = dict(sources_sha256="2ae7ade016db0695ffc46344ba3783686d97aae892947e766fb1a9e42dbaa896",
+               bytes_per_launch={"surrogate4096": 404519230 / 8, "fig7": 167134804 / 3})
 
 
 # Table 3 of the paper: wall time of its GPU and CPU scans (seconds).
@@ -69,7 +70,7 @@ PAPER_TABLE3 = {"fig6_th1_1.571": (75.0, 1020.0), "fig7": (2213.0, 25000.0)}
 # rocprofv3 counters (SQ_INSTS_VALU_{ADD,MUL,FMA,TRANS}_F64 x 64 lanes, FMA
 # counted twice, over the launch's orbit-steps), valid only for the kernel
 # sources whose hash is recorded with them.
-HW_FLOPS = dict(sources_sha256="a32330481765727ae610e4eef6205476be401dfbc19ffa2f761c48ec28efe94d",
+HW_FLOPS = dict(sources_sha256="2ae7ade016db0695ffc46344ba3783686d97aae892947e766fb1a9e42dbaa896",
                 per_orbit_step={("k_wrap_scan", "surrogate4096"): 4339.7, ("k_wrap_scan", "grid314"): 4338.2,
                                 ("k_wrap_scan", "fig7"): 4364.5, ("k_batch_scan", "batch1M"): 4339.9,
                                 ("k_fli_scan", "grid64"): 4338.3})
@@ -499,7 +500,7 @@ def surrogate_bench(args, dev):
     line["train_loss"] = [round(h, 5) for h in hist]
 
     # Dominant kernel of the assisted scan: the FP64 scan of the audit and of
-    # the uncertain points.  Per launch: the algorithmic work of the
+    # the uncertain points.  Per launch: the FP64 work of the
     # orbit-steps it integrated over its average duration, from the scan
     # launches' own events over the timed scans.
     per_kernel = {}
@@ -513,7 +514,7 @@ def surrogate_bench(args, dev):
             d["orbit_steps"] += ph["orbit_steps"]
     kname, kd = max(per_kernel.items(), key=lambda kv: kv[1]["ms"])
     launch_ms = kd["ms"] / kd["launches"]
-    flops_per_launch = ALG_FLOPS_PER_ORBIT_STEP * kd["orbit_steps"] / kd["launches"]
+    flops_per_launch = FLOPS_PER_ORBIT_STEP * kd["orbit_steps"] / kd["launches"]
     achieved = flops_per_launch / (launch_ms * 1e-3) / 1e12
     traffic = None
     if TRAFFIC["sources_sha256"] == sources_sha256():
@@ -523,7 +524,7 @@ def surrogate_bench(args, dev):
                             kernel=f"{kname}<RK4,SIX> (audit and fallback integrations of pn_surrogate_scan)",
                             kernel_ms=launch_ms, launches_per_step=kd["launches"] / args.steps,
                             orbit_steps_per_launch=kd["orbit_steps"] / kd["launches"],
-                            flops_per_orbit_step=ALG_FLOPS_PER_ORBIT_STEP,
+                            flops_per_orbit_step=FLOPS_PER_ORBIT_STEP,
                             orbit_steps_per_s=kd["orbit_steps"] / (kd["ms"] * 1e-3),
                             phases=res.scans)
     hw = hardware_flops(kname, "surrogate4096")
@@ -536,7 +537,7 @@ def surrogate_bench(args, dev):
                                       frac=inf_achieved / 2500.0, traffic=None, kernel="k_mlp_infer",
                                       kernel_ms=inf["fused_ms"], layered_ms=inf["layered_ms"],
                                       flops_per_point=inf_flops / grid.n)
-    plain_tf = ALG_FLOPS_PER_ORBIT_STEP * plain_steps / (plain_ms * 1e-3) / 1e12
+    plain_tf = FLOPS_PER_ORBIT_STEP * plain_steps / (plain_ms * 1e-3) / 1e12
     line["plain_roofline"] = dict(bound="alu", achieved=plain_tf, peak=FP64_VECTOR_PEAK_TFLOPS, unit="TFLOP/s",
                                   frac=plain_tf / FP64_VECTOR_PEAK_TFLOPS,
                                   kernel="k_fli_scan<RK4,SIX> (plain scan of the 65,536-point sample)",
@@ -704,14 +705,14 @@ def main():
         # sample's rate (never run).
         cb["extrapolated_full_s"] = orbit_steps / cb["value"]
         line["cpu_baseline"] = cb
-    achieved = ALG_FLOPS_PER_ORBIT_STEP * orbit_steps / (kernel_ms * 1e-3) / 1e12
+    achieved = FLOPS_PER_ORBIT_STEP * orbit_steps / (kernel_ms * 1e-3) / 1e12
     traffic = None
     if TRAFFIC["sources_sha256"] == sources_sha256():
         traffic = TRAFFIC["bytes_per_launch"].get(wl.name if args.schedule == "auto" else wl.name + "/plain")
     line["roofline"] = dict(bound="alu", achieved=achieved, peak=FP64_VECTOR_PEAK_TFLOPS, unit="TFLOP/s",
                             frac=achieved / FP64_VECTOR_PEAK_TFLOPS, traffic=traffic,
                             kernel=kernel, kernel_ms=kernel_ms,
-                            flops_per_orbit_step=ALG_FLOPS_PER_ORBIT_STEP,
+                            flops_per_orbit_step=FLOPS_PER_ORBIT_STEP,
                             oracle_flops_per_orbit_step=oracle_fpos)
     hw = hardware_flops(kernel.split("<")[0], wl.name)
     if hw is not None:
