@@ -1883,7 +1883,7 @@ pn_status pn_surrogate_scan(pn_mlp* net, int32_t* adam_step, const pn_model* mod
         // and trains on each while the next is drawn (a draw costs a third of
         // its epoch's training).  2,640 points, 40 epochs: 0.6 ms in one group.
         const int64_t per_copy =
-            nv > 0 ? std::max<int64_t>(1, std::min<int64_t>((int64_t)N / nv, (cfg->refine_epochs + 4) / 5)) : 1;
+            nv > 0 ? std::max<int64_t>(1, std::min<int64_t>((int64_t)N / nv, (cfg->refine_epochs - 1) / 5 + 1)) : 1;
         // Two host buffers in turn, each refilled once its copy is done; they
         // outlive every copy, also where a call in between fails.
         std::vector<int32_t> orders[2];
@@ -1917,8 +1917,8 @@ pn_status pn_surrogate_scan(pn_mlp* net, int32_t* adam_step, const pn_model* mod
             copies.pending[buf] = true;
             for (int32_t k = 0; k < ne; ++k) {
                 const int32_t e = e0 + k;
-                // The transposed weight copies are formed before the first
-                // refinement step; each step's Adam update keeps them current.
+                // The weights' other layouts are formed before the first
+                // refinement step; each step's update keeps them current.
                 const float lr_e = cfg->refine_cosine
                                        ? cfg->refine_lr * 0.5f *
                                              (1.0f + cosf(3.14159265358979f * e / cfg->refine_epochs))
